@@ -223,7 +223,7 @@ def work(case):
         return {"bytes": cycle + n[0] * 2 * k * w, "flops": cycle_flops}
     wk = max(w, 4)
     # a fixed count of steps, or about what 1e-11 takes from x = 0 on these grids
-    steps = case["steps"] or int(8 * n[0] ** (1 / 4.5))
+    steps = case["steps"] or int(20 * (n[0] / 4096) ** 0.32)
     solves = 2 if kind == "adjoint" else 1
     basis = sum(2 * (i % RESTART + 1) * n[0] * wk * k for i in range(steps))
     cycles = (steps + RESTART - 1) // RESTART
