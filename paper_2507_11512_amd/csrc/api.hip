@@ -39,6 +39,7 @@ struct Level {
     // [1] float, [2] __half, [3] bf16
     void *r[4] = {nullptr, nullptr, nullptr, nullptr};
     void *z[4] = {nullptr, nullptr, nullptr, nullptr};
+    void *z2[4] = {nullptr, nullptr, nullptr, nullptr};  // second z of the tiled sweeps, where they are used
 };
 
 // How the SpMV after a V-cycle shares its work with the V-cycle's last
@@ -82,6 +83,7 @@ struct Batch {
     double *partials = nullptr;                              // kMaxBasis * K columns
     double *host_scal = nullptr;                             // pinned scalar blocks
     void *lr[2][kMaxLevels] = {}, *lz[2][kMaxLevels] = {};  // levels >= 1, [0] double, [1] float
+    void *lz2[2][kMaxLevels] = {};                          // second z of the tiled sweeps, where they are used
     Krylov kry[2];                                           // per vector type
     void *tmp[2][3] = {};                                    // ABI staging and autotuning
     BatchTune tune[4];                                       // per matrix precision (Prec)
@@ -168,6 +170,9 @@ struct hpgmx_ctx {
         owned.push_back(p);
         return p;
     }
+
+    // Whether the bound workspace, if there is one, still has room for `bytes`.
+    bool fits(size_t bytes) const { return !ws_base || ws_used + round_up(bytes) <= ws_size; }
 
     // profiling scopes around single launches
     void prof_begin(int kernel, int level)
@@ -310,6 +315,28 @@ void zero_entry(hpgmx_ctx *c, void *v, i64 N, Prec p)
               "hipMemsetAsync");
 }
 
+// Levels whose half-sweeps run as one launch each (launch_sweep): those
+// where a launch per colour is bound by latency, up to kSweepBytes bytes of
+// matrix values per slot (times right-hand sides).  Beyond it the halo rows
+// cost more than the launches: a 30-step cycle with 3 levels takes, with
+// colour launches and with tiles on level 0 too, 4457 and 3204 us at 24^3,
+// 5467 and 4205 at 64^3 and 7561 and 6238 at 96^3 in FP32 (0.9M rows), 6391
+// and 4788 at 64^3, 7593 and 7070 at 80^3 (0.5M) and 10170 either way at
+// 96^3 in FP64, where a 96 x 88 x 80 level in tiles lost 2 %.  A handle
+// with a pair_rows of its own gets the launches it asks for, and a profiled
+// solve the launches that are timed one by one.
+constexpr i64 kSweepBytes = 1 << 22;
+bool tiled_size(const Layout &lay, i64 N, int K, Prec p)
+{
+    const i64 vb = matrix_prec(p) == P64 ? 8 : matrix_prec(p) == P32 ? 4 : 2;
+    return lay.pair_rows == kDefaultPairRows && N * K * vb <= kSweepBytes;
+}
+bool tiled(const hpgmx_ctx *c, int l, Prec p, int K)
+{
+    const Matrix &A = c->lv[l].A;
+    return !c->prof && tiled_size(c->layout, A.g.N, K, p) && sweep_possible(A, K, p);
+}
+
 void ensure_level_vectors(hpgmx_ctx *c, Prec p)
 {
     const int vt = vt_of(p);
@@ -319,6 +346,8 @@ void ensure_level_vectors(hpgmx_ctx *c, Prec p)
             L.r[vt] = gathered_vector(c, L.A.g.N, p);
             L.z[vt] = gathered_vector(c, L.A.g.N, p);
         }
+        const size_t b = (size_t)L.A.g.N * vec_bytes(p);
+        if (!L.z2[vt] && tiled_size(c->layout, L.A.g.N, 1, p) && c->fits(b)) L.z2[vt] = c->dalloc(b);
     }
 }
 
@@ -407,6 +436,10 @@ size_t plan_bytes(const hpgmx_problem_desc &pd, const hpgmx_mg_desc &mg, int m, 
                 const bool want = vt == 0 ? (mask & 1u) != 0 : vt == 1 ? (mask & 0xEu) != 0
                                                                        : (mask >> (vt + 2)) & 1u;
                 if (want) { add((N + 1) * vt_bytes[vt]); add((N + 1) * vt_bytes[vt]); }
+                bool second = false;  // the tiled sweeps' second z
+                for (int p = 0; p < kNumPrec; ++p)
+                    second = second || (((mask >> p) & 1u) && vt_of((Prec)p) == vt && tiled_size(lay, (i64)N, 1, (Prec)p));
+                if (second) add(N * vt_bytes[vt]);
             }
         nx /= 2; ny /= 2; nz /= 2;
     }
@@ -458,6 +491,31 @@ void sweep_colours(hpgmx_ctx *c, int l, Prec p, const void *r, void *z, bool for
         if (n == 7) { o.w = out.w; o.scale = out.scale; }
         else if (n >= kSplitFirst && out.part) { o.part = out.part; o.forward = forward; }
         launch_gs_colour(A, p, col, mode, r, z, c->stream, o);
+    }
+}
+
+// Half-sweeps (eight colours each) of n sweeps of a kind.
+int half_sweeps(int kind, int n) { return kind == HPGMX_GS_SYMMETRIC ? 2 * n : n; }
+
+// `nsweeps` > 0 sweeps of kind `kind` on level l for K right-hand sides, one
+// launch per half-sweep (tiled()): from the values in `src` (null: from
+// zero) to `z`.  The half-sweeps alternate between z and `other`, so that
+// none writes what it reads: src is z for an even count of half-sweeps and
+// `other` for an odd one.  With zc the first corrects its input by P zc, with
+// rc the last restricts its residual (see launch_sweep).
+void tiled_sweeps(hpgmx_ctx *c, int l, Prec p, int K, int kind, int nsweeps, const void *r, const void *src,
+                  void *z, void *other, const void *zc, void *rc)
+{
+    const int half = half_sweeps(kind, nsweeps);
+    for (int h = 0; h < half; ++h) {
+        const bool symm = kind == HPGMX_GS_SYMMETRIC, back = symm ? (h & 1) : kind == HPGMX_GS_BACKWARD;
+        void *dst = (half - h) & 1 ? z : other;
+        const bool last = h == half - 1;
+        // the backward half of a symmetric sweep leaves colour 7 as it is: its neighbours are unchanged
+        launch_sweep(c->lv[l].A, p, K, !back, symm && back, r, src,
+                     l + 1 < (int)c->lv.size() ? &c->lv[l + 1].A.g : nullptr, h == 0 ? zc : nullptr, dst,
+                     last ? rc : nullptr, c->stream);
+        src = dst;
     }
 }
 
@@ -518,13 +576,47 @@ void presmooth_restrict(hpgmx_ctx *c, int l, Prec p, int kind, int nsweeps, cons
         launch_restrict(c->lv[l].A, gc, p, r, z, rc, c->stream);
 }
 
+// Whether a V-cycle runs level l in tiles, with z2 as its second vector.
+bool tiled_level(const hpgmx_ctx *c, int l, Prec p, int K, const void *z2)
+{
+    const hpgmx_mg_desc &mg = c->mg;
+    const bool smooths = l == mg.levels - 1 ? mg.coarsest_sweeps > 0 : mg.pre_sweeps > 0 && mg.post_sweeps > 0;
+    return z2 && smooths && tiled(c, l, p, K);
+}
+
+// A V-cycle level in tiles; coarse(rc, zc) runs the coarser levels.
+template <typename F>
+void tiled_vcycle(hpgmx_ctx *c, int l, Prec p, int K, const void *r, void *z, void *z2, void *rc, const void *zc,
+                  F &&coarse)
+{
+    const hpgmx_mg_desc &mg = c->mg;
+    if (l == mg.levels - 1) {
+        tiled_sweeps(c, l, p, K, mg.sweep, mg.coarsest_sweeps, r, nullptr, z, z2, nullptr, nullptr);
+        return;
+    }
+    // the pre-sweeps end in the vector that the post-sweeps, which end in z, start from
+    void *x = half_sweeps(mg.sweep, mg.post_sweeps) & 1 ? z2 : z;
+    tiled_sweeps(c, l, p, K, mg.sweep, mg.pre_sweeps, r, nullptr, x, x == z ? z2 : z, nullptr, rc);
+    coarse();
+    tiled_sweeps(c, l, p, K, mg.sweep, mg.post_sweeps, r, x, z, z2, zc, nullptr);
+}
+
 // z = M^{-1} r on level l (z is overwritten; the cycle starts from zero).
 // With out.w (level 0 only, see fused_spmv_colour) the last colour launch
-// also writes its rows of w = A z.
-void vcycle(hpgmx_ctx *c, int l, Prec p, const void *r, void *z, SpmvOut out = {})
+// also writes its rows of w = A z.  z2: a second vector of z's size on level
+// 0 (the other levels have their own) for the tiled sweeps, which write no
+// SpMV rows.
+void vcycle(hpgmx_ctx *c, int l, Prec p, const void *r, void *z, SpmvOut out = {}, void *z2 = nullptr)
 {
     const hpgmx_mg_desc &mg = c->mg;
     const int vt = vt_of(p);
+    if (l > 0) z2 = c->lv[l].z2[vt];
+    if (!out.w && !out.part && tiled_level(c, l, p, 1, z2)) {
+        const bool leaf = l == mg.levels - 1;
+        tiled_vcycle(c, l, p, 1, r, z, z2, leaf ? nullptr : c->lv[l + 1].r[vt], leaf ? nullptr : c->lv[l + 1].z[vt],
+                     [&]() { vcycle(c, l + 1, p, c->lv[l + 1].r[vt], c->lv[l + 1].z[vt]); });
+        return;
+    }
     if (l == mg.levels - 1) {
         smooth_level(c, l, p, mg.sweep, r, z, true, mg.coarsest_sweeps);
         return;
@@ -727,8 +819,11 @@ hpgmx_status solve(hpgmx_ctx *c, const double *b, double *x, const hpgmx_solve_d
                     // the V-cycle's last colour launch, the others from the
                     // SpMV; with kSpmvSplit the launches at sweep positions
                     // 2-6 also leave partial sums for their rows
+                    // (tiled sweeps leave all of it to the SpMV: the same bits)
                     const int fc = fused_spmv_colour(c);
-                    const int sm = fc < 0 ? kSpmvPlain : c->spmv_mode;
+                    int sm = fc < 0 ? kSpmvPlain : c->spmv_mode;
+                    if (tiled_level(c, 0, p, 1, K.part))
+                        sm = sm == kSpmvLast ? kSpmvPlain : sm == kSpmvSplit ? kSpmvSplitSeparate : sm;
                     SpmvOut out{};
                     if (sm == kSpmvLast || sm == kSpmvSplit) { out.w = col(k + 1); out.scale = spmv_scale(p, c->ctrl, k); }
                     if (sm == kSpmvSplit) out.part = K.part;
@@ -737,9 +832,9 @@ hpgmx_status solve(hpgmx_ctx *c, const double *b, double *x, const hpgmx_solve_d
                             ProfScope ps(c, HPGMX_K_CAST, 0);
                             launch_cast_mg(N, p, (const float *)col(k), c->ctrl, false, k, K.r0, c->stream);
                         }
-                        vcycle(c, 0, p, K.r0, K.z, out);
+                        vcycle(c, 0, p, K.r0, K.z, out, K.part);
                     } else {
-                        vcycle(c, 0, p, col(k), K.z, out);
+                        vcycle(c, 0, p, col(k), K.z, out, K.part);
                     }
                     {
                         ProfScope ps(c, HPGMX_K_SPMV, 0);
@@ -800,9 +895,9 @@ hpgmx_status solve(hpgmx_ctx *c, const double *b, double *x, const hpgmx_solve_d
                     ProfScope ps(c, HPGMX_K_CAST, 0);
                     launch_cast_mg(N, p, (const float *)K.u, c->ctrl, true, kk, K.r0, c->stream);
                 }
-                vcycle(c, 0, p, K.r0, K.z);
+                vcycle(c, 0, p, K.r0, K.z, {}, K.part);
             } else {
-                vcycle(c, 0, p, K.u, K.z);
+                vcycle(c, 0, p, K.u, K.z, {}, K.part);
             }
             {
                 ProfScope ps(c, HPGMX_K_UPDATE, 0);
@@ -1615,8 +1710,16 @@ hpgmx_status hpgmx_smooth(hpgmx_handle h, int level, int dtype, int sweep, const
         zero_entry(h, h->tmp[vt][1], A.g.N, pv);
         launch_nat2int(A.g, pv, r, pv, h->tmp[vt][0], h->stream);
         if (!zero_guess) launch_nat2int(A.g, pv, z, pv, h->tmp[vt][1], h->stream);
-        smooth_level(h, level, p, sweep, h->tmp[vt][0], h->tmp[vt][1], zero_guess != 0, 1);
-        launch_int2nat(A.g, pv, h->tmp[vt][1], pv, z, h->stream);
+        void *out = h->tmp[vt][1];
+        if (tiled(h, level, p, 1)) {
+            void *other = h->tmp[vt][2];
+            if (half_sweeps(sweep, 1) & 1) std::swap(out, other);
+            tiled_sweeps(h, level, p, 1, sweep, 1, h->tmp[vt][0], zero_guess ? nullptr : h->tmp[vt][1], out, other,
+                         nullptr, nullptr);
+        } else {
+            smooth_level(h, level, p, sweep, h->tmp[vt][0], out, zero_guess != 0, 1);
+        }
+        launch_int2nat(A.g, pv, out, pv, z, h->stream);
         return HPGMX_OK;
     });
 }
@@ -1636,7 +1739,7 @@ hpgmx_status hpgmx_vcycle(hpgmx_handle h, int dtype, const void *r, void *z)
         const Prec pv = vprec(p);
         zero_entry(h, h->tmp[vt][1], A.g.N, pv);
         launch_nat2int(A.g, pv, r, pv, h->tmp[vt][0], h->stream);
-        vcycle(h, 0, p, h->tmp[vt][0], h->tmp[vt][1]);
+        vcycle(h, 0, p, h->tmp[vt][0], h->tmp[vt][1], {}, h->tmp[vt][2]);
         launch_int2nat(A.g, pv, h->tmp[vt][1], pv, z, h->stream);
         return HPGMX_OK;
     });

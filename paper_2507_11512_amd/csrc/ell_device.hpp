@@ -109,6 +109,8 @@ __device__ __forceinline__ void stage_colmap(int *lds, const int *__restrict__ c
     __syncthreads();
 }
 
+constexpr unsigned kAllSlots = (1u << kSlots) - 1u;
+
 // sum over the slots in MASK of a(p,s) * x[col(p,s)] (slot order), in the
 // arithmetic type T; x may be stored in a narrower type X (the 16-bit
 // multigrid vectors), widened after the gathers.  Columns: C16 = false,
@@ -148,7 +150,6 @@ __device__ __forceinline__ T ell_row_dot(const V *__restrict__ offv, const void 
     return acc;
 }
 
-constexpr unsigned kAllSlots = (1u << kSlots) - 1u;
 
 // One SpMV row from its parts: (a_pp x_p + acc) * scale, acc the slot sum of
 // ell_row_dot.  Contraction is off so that the SpMV kernel and the last
@@ -213,6 +214,43 @@ __device__ __forceinline__ T ell_row_dot2(const V *__restrict__ offv, const void
     for (int s = 0; s < kSlots; ++s) {
         if (MASK & (1u << s)) acc = madd(to_t<T>(a[s]), to_t<T>(xv[s]), acc);
         if (EMASK & MASK & (1u << s)) ae = madd(to_t<T>(a[s]), to_t<T>(xv[s]), ae);
+    }
+    accE = ae;
+    return acc;
+}
+
+// As ell_row_dot over all slots, split in two: accE over the slots in `early`,
+// which may differ from lane to lane, the result over the others.
+template <typename T, typename V, bool C16, typename X>
+__device__ __forceinline__ T ell_row_dot_split(const V *__restrict__ offv, const void *__restrict__ offc,
+                                               const X *x, const EllRow &er, i64 p, const int *Dc, i64 N,
+                                               unsigned early, T &accE)
+{
+    V a[kSlots];
+    int ci[kSlots];
+    unsigned w[kPairs];
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s) {
+        const i64 e = er.base + (i64)s * er.stride;
+        a[s] = offv[e];
+        if constexpr (!C16) ci[s] = static_cast<const int *>(offc)[e];
+    }
+    if constexpr (C16) load_pairs<kAllSlots>(static_cast<const unsigned *>(offc), er, w);
+    sched_fence();
+    X xv[kSlots];
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s) {
+        if constexpr (C16) xv[s] = x[ell_col(pair_half(w[s >> 1], s), p, Dc[s], N)];
+        else xv[s] = x[ci[s]];
+    }
+    sched_fence();
+    T acc = (T)0, ae = (T)0;
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s) {
+        const bool e = early >> s & 1u;
+        const T v = madd(to_t<T>(a[s]), to_t<T>(xv[s]), e ? ae : acc);
+        ae = e ? v : ae;
+        acc = e ? acc : v;
     }
     accE = ae;
     return acc;

@@ -309,6 +309,16 @@ void launch_gs_colour(const Matrix &A, Prec p, int c, int mode, const void *r, v
 void launch_gs_pair_zero(const Matrix &A, Prec p, int a, bool forward, const void *r, void *z,
                          hipStream_t s);
 bool gs_pair_possible(const Matrix &A);
+// A half-sweep (all eight colours) in one launch, bit-identical to the
+// colour launches.  zin: the old values (null: a sweep from zero); zout: the
+// new ones, another vector than zin.  zc (with gc, the coarse level): the
+// prolongation-correction zin + P zc is formed first.  rc (with gc): the
+// launch also restricts the residual of zout, as launch_restrict_after_sweep
+// for a sweep from zero and as launch_restrict otherwise.  skip_first: the
+// first colour is left as it is in zin.  K interleaved right-hand sides.
+bool sweep_possible(const Matrix &A, int K, Prec p);
+void launch_sweep(const Matrix &A, Prec p, int K, bool forward, bool skip_first, const void *r, const void *zin,
+                  const Geom *gc, const void *zc, void *zout, void *rc, hipStream_t s);
 void launch_restrict(const Matrix &Af, const Geom &gc, Prec p, const void *r, const void *z,
                      void *rc, hipStream_t s);
 // The same result when z is the outcome of a single Gauss-Seidel sweep from

@@ -1,0 +1,454 @@
+// A whole Gauss-Seidel half-sweep (eight colours) in one launch, for the
+// levels where a launch per colour is bound by latency.
+//
+// A workgroup owns a tile of the level -- whole x-lines, n cells in y and m
+// in z (a cell is two grid lines) -- and relaxes the eight colours of its
+// tile one after the other in LDS, with a workgroup barrier in place of the
+// kernel boundary.  A colour of the tile needs the new values of earlier
+// colours in its neighbours, so each colour is relaxed on the tile plus the
+// halo that the later colours reach: the chain of colours moves at most three
+// cells in y and one in z (see sweep_args), never across workgroups.  Halo rows
+// are relaxed by every workgroup that needs them, from the same old values
+// with the same operations, so all copies agree and the result equals the
+// colour launches bit for bit; the sweep reads its old values from one
+// vector and writes the new ones to another, because a neighbouring
+// workgroup may still need the old ones.  No workgroup waits for another.
+//
+// What bounds it: latency.  A colour launch on a small level is two dependent
+// memory round trips (the row's entries, then its neighbours) and a kernel
+// boundary, 3-6 us whatever the row count; here the entries of the next
+// colour's rows, which depend on no z, are loaded while the current colour
+// is relaxed, the neighbours come from LDS, and a colour takes about 0.8 us
+// (issue of the row's 26 loads, 26 LDS reads and 26 dependent FMAs).  The
+// price is the halo (1.5 to 4 times the rows).  Measured, FP32 forward, the
+// eight launches with their gaps against this one: 64^3 level 45 -> 12 us
+// from zero with the restriction, 14 us with the prolongation; 32^3 36 ->
+// 11; 16^3 27 -> 9.  Solves of 16^3 (symmetric) 6.5 -> 3.6 ms, 48 x 40 x 32
+// 9.9 -> 5.5 ms, 128^3 63 -> 52.5 ms.
+//
+// The tile's z lies in LDS with the same strides for every colour, each line
+// followed by a zero cell and the lines outside the grid zero, so a
+// neighbour's cell is the row's own plus an offset that depends on the
+// colour and the slot only (the colour-blocked order puts every neighbour at
+// a fixed offset; the padded slots fall on the zeros).  The rows' values come
+// from the stored matrix.
+#include "ell_device.hpp"
+
+#include <algorithm>
+#include <stdexcept>
+#include <type_traits>
+
+namespace hpgmx {
+
+constexpr int kSweepThreads = 512;        // at most; two waves per SIMD, 256 VGPRs each
+constexpr int kCus = 256;
+constexpr size_t kSweepLds = 64 * 1024;   // bytes of z a workgroup may hold
+
+// A launch's tiles.  Boxes are in cells, relative to the tile's first cell,
+// and not clipped to the grid.
+struct SweepArgs {
+    // per sweep position (8: the restriction) the rows worked on and the
+    // neighbours read: jlo + 8, jn, klo + 8, kn in 4, 5, 4, 5 bits, then bit
+    // f - 1 for the slots to colour c ^ f
+    unsigned pos[9];
+    int off[8];            // first row of each colour
+    int nx1, ny1, nz1;     // extents + 1
+    int n, m, tj;          // cells per tile in y and z, tiles in y
+    int remap, forward;
+    int first, tail;       // first sweep position; 0, or the restriction after the sweep: 1 from the slots to
+                           // colours relaxed after colour 4, 2 r - A z
+    int sx, pj, pk;        // cells per line (the zero included), lines per plane and planes held per colour
+    int hj, hk;            // the held box's first line and plane
+    int coff[8], cnx1, cny1;  // the coarse level (restriction, prolongation)
+};
+__host__ __device__ inline unsigned pack_pos(int jlo, int jn, int klo, int kn, unsigned flips)
+{
+    return (unsigned)(jlo + 8) | (unsigned)jn << 4 | (unsigned)(klo + 8) << 9 | (unsigned)kn << 13 | flips << 18;
+}
+
+namespace {
+
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// t / d for 0 <= t < 2^20 and 1 <= d, with rd the hardware's 1 / d: (t + 1/2) / d
+// is at least 1/(2d) away from an integer, and the product's relative error
+// (below 2^-21) is smaller than that for these t.
+__device__ __forceinline__ int small_div(int t, float rd) { return (int)(((float)t + 0.5f) * rd); }
+__device__ __forceinline__ float recip(int d) { return __builtin_amdgcn_rcpf((float)d); }
+
+// Element `soff + e` (soff the same for every lane) of an array below 2^32 bytes.
+template <typename E> __device__ __forceinline__ E ld_at(const void *base, unsigned soff, unsigned e)
+{
+    const char *b = static_cast<const char *>(base) + soff * sizeof(E);
+    return *reinterpret_cast<const E *>(b + e * (unsigned)sizeof(E));
+}
+
+// Internal index of coarse point (I, J, K).
+__device__ __forceinline__ int coarse_index(const SweepArgs &P, int I, int J, int K)
+{
+    const int c = colour_of(I, J, K);
+    int off = P.coff[0];
+#pragma unroll
+    for (int q = 1; q < 8; ++q) off = c == q ? P.coff[q] : off;
+    const int bx = (P.cnx1 - (I & 1)) >> 1, by = (P.cny1 - (J & 1)) >> 1;
+    return off + (I >> 1) + bx * ((J >> 1) + by * (K >> 1));
+}
+
+__host__ __device__ constexpr int slot_flip(int s)
+{
+    const int t = s < 13 ? s : s + 1;
+    return ((t % 3 - 1) & 1) | (((t / 3) % 3 - 1) & 1) << 1 | ((t / 9 - 1) & 1) << 2;
+}
+
+// One row's entries, loaded ahead of its relaxation.
+template <typename V, typename S> struct SweepRow {
+    V a[kSlots];
+    S r;
+    V d;
+    int cell;         // its own, times K, plus the right-hand side
+    int ii, jj, kk;   // in its colour block
+    bool act;
+};
+
+}  // namespace
+
+// K interleaved right-hand sides, one per lane (K lanes share a row).
+template <typename V, typename S, int K>
+__global__ __launch_bounds__(kSweepThreads) void k_sweep(const SweepArgs P, const V *__restrict__ offv,
+                                                         const V *__restrict__ diag, const S *__restrict__ r,
+                                                         const S *__restrict__ zin, const S *__restrict__ zc,
+                                                         S *__restrict__ zout, S *__restrict__ rc)
+{
+    using T = typename VecT<V>::T;
+    using Row = SweepRow<V, S>;
+    constexpr unsigned kChunk = 1u << kDefaultEllChunkLog2;
+    extern __shared__ __align__(16) unsigned char smem[];
+    S *zs = reinterpret_cast<S *>(smem);
+    const int tid = threadIdx.x, nt = blockDim.x;
+    const int rhs = K > 1 ? tid % K : 0;
+    const int tile = (int)xcd_tile(blockIdx.x, gridDim.x, P.remap);
+    const int kt = tile / P.tj, K0 = kt * P.m, J0 = (tile - kt * P.tj) * P.n;
+    const int plane = P.sx * P.pj, block = plane * P.pk;  // cells
+    const int bxe = P.nx1 >> 1;                           // the longer of the two line lengths
+    const float rbx = recip(bxe);
+    auto colour = [&](int pos) { return pos == 8 ? 4 : P.forward ? pos : 7 - pos; };
+    auto ext_x = [&](int c) { return (P.nx1 - (c & 1)) >> 1; };
+    auto ext_y = [&](int c) { return (P.ny1 - ((c >> 1) & 1)) >> 1; };
+    auto ext_z = [&](int c) { return (P.nz1 - (((c >> 2) & 1) ^ 1)) >> 1; };
+
+    // loads this lane's row of chunk `chunk` of position pos
+    auto fetch = [&](int pos, int chunk, Row &E) {
+        const unsigned q = P.pos[pos];
+        const int c = colour(pos), jn = q >> 4 & 31, jlo = (int)(q & 15) - 8, klo = (int)(q >> 9 & 15) - 8;
+        const int kn = q >> 13 & 31;
+        const int t = (chunk * nt + tid) / K;
+        const int line = small_div(t, rbx), ii = t - line * bxe;
+        const int kq = small_div(line, recip(jn)), jr = jlo + (line - kq * jn), kr = klo + kq;
+        const int jj = J0 + jr, kk = K0 + kr;
+        const int bx = ext_x(c), by = ext_y(c);
+        E.act = kq < kn && ii < bx && (unsigned)jj < (unsigned)by && (unsigned)kk < (unsigned)ext_z(c);
+        E.cell = (1 + c * block + ii + P.sx * ((jr - P.hj) + P.pj * (kr - P.hk))) * K + rhs;
+        E.ii = ii; E.jj = jj; E.kk = kk;
+        if (!E.act) return;
+        const int p = P.off[c] + ii + bx * (jj + by * kk);
+        E.r = r[(i64)p * K + rhs];
+        E.d = diag[p];
+        const unsigned e = ((unsigned)p / kChunk) * (kSlots * kChunk) + (unsigned)p % kChunk;
+#pragma unroll
+        for (int f = 1; f < 8; ++f) {
+            if (q >> (17 + f) & 1u) {
+#pragma unroll
+                for (int s = 0; s < kSlots; ++s)
+                    if (slot_flip(s) == f) E.a[s] = ld_at<V>(offv, s * kChunk, e);
+            } else {  // not read: adds 0
+#pragma unroll
+                for (int s = 0; s < kSlots; ++s)
+                    if (slot_flip(s) == f) E.a[s] = from_t<V>((T)0);
+            }
+        }
+    };
+
+    // sum over the slots of a z, the z gathered from LDS, in slot order
+    auto row_sum = [&](int pos, const Row &E) -> T {
+        const int c = colour(pos);
+        // cell of the neighbour minus the row's own: an even line's (or
+        // plane's) neighbours are the odd ones of the cell before and of its
+        // own, an odd one's the even ones of its own cell and of the one after
+        const bool xo = c & 1, yo = c & 2, zo = !(c & 4);  // colours 0-3 lie on the odd planes
+        const int fx = (xo ? -block : block) + (xo ? 0 : -1), fy = yo ? -2 * block : 2 * block,
+                  fz = (c & 4) ? -4 * block : 4 * block;
+        const int dy[3] = {fy - (yo ? 0 : P.sx), 0, fy + (yo ? P.sx : 0)};
+        const int dz[3] = {fz - (zo ? 0 : plane), 0, fz + (zo ? plane : 0)};
+        S xv[kSlots];
+#pragma unroll
+        for (int g = 0; g < 9; ++g) {  // lines dk, dj
+            const int at = E.cell + (dz[g / 3] + dy[g % 3]) * K;
+            const S *x = zs + (at + fx * K);
+            const int s = 3 * g - (g > 4 ? 1 : 0);  // slot of di = -1
+            xv[s] = x[0];
+            if (g != 4) xv[s + 1] = zs[at];
+            xv[g == 4 ? s + 1 : s + 2] = x[K];
+        }
+        T acc = (T)0;
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) acc = madd(to_t<T>(E.a[s]), to_t<T>(xv[s]), acc);
+        return acc;
+    };
+
+    const int last = P.tail ? 8 : 7;
+    auto chunks = [&](int pos) {
+        const unsigned q = P.pos[pos];
+        return (bxe * (int)(q >> 4 & 31) * (int)(q >> 13 & 31) * K + nt - 1) / nt;
+    };
+
+    Row A, B;
+    int pos = P.first, chunk = 0, nchunks = chunks(pos);
+    fetch(pos, 0, A);
+
+    // z: the old values, or zero
+    if (zin) {
+        if (tid < K) zs[tid] = from_t<S>((T)0);
+        const float rsx = recip(P.sx), rpj = recip(P.pj);
+        for (int e = tid; e < block * K; e += nt) {
+            const int t = e / K, line = small_div(t, rsx), ii = t - line * P.sx;
+            const int kq = small_div(line, rpj), jj = J0 + P.hj + (line - kq * P.pj), kk = K0 + P.hk + kq;
+            S v[8], w = from_t<S>((T)0);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const int bx = ext_x(c), by = ext_y(c);
+                v[c] = from_t<S>((T)0);
+                if (ii < bx && (unsigned)jj < (unsigned)by && (unsigned)kk < (unsigned)ext_z(c)) {
+                    v[c] = zin[(i64)(P.off[c] + ii + bx * (jj + by * kk)) * K + rhs];
+                    if (c == 4 && zc) w = zc[(i64)coarse_index(P, ii, jj, kk) * K + rhs];
+                }
+            }
+            sched_fence();
+            if (zc) v[4] = from_t<S>(to_t<T>(v[4]) + to_t<T>(w));
+#pragma unroll
+            for (int c = 0; c < 8; ++c) zs[(1 + c * block + t) * K + rhs] = v[c];
+        }
+    } else {
+        const int words = ((1 + 8 * block) * K * (int)sizeof(S) + 15) / 16;
+        for (int e = tid; e < words; e += nt) reinterpret_cast<uint4 *>(smem)[e] = uint4{0, 0, 0, 0};
+    }
+    lds_barrier();
+
+    // one chunk of rows: E holds its entries, F takes those of the next one
+    auto step = [&](Row &E, Row &F) -> bool {
+        int npos = pos, nchunk = chunk + 1;
+        if (nchunk == nchunks) {
+            npos = pos + 1;
+            nchunk = 0;
+        }
+        // E was loaded during the chunk before: wait for it before the next
+        // loads go out, not behind them
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+        sched_fence();
+        if (npos <= last) fetch(npos, nchunk, F);
+        sched_fence();
+        if (E.act) {
+            const T acc = row_sum(pos, E);
+            if (pos < 8) {
+                zs[E.cell] = from_t<S>((to_t<T>(E.r) - acc) / to_t<T>(E.d));
+            } else {  // the colour-4 block is the coarse level in its natural order
+                const T v = P.tail == 1 ? -acc : to_t<T>(E.r) - (to_t<T>(E.d) * to_t<T>(zs[E.cell]) + acc);
+                rc[(i64)coarse_index(P, E.ii, E.jj, E.kk) * K + rhs] = from_t<S>(v);
+            }
+        }
+        if (npos > last) return true;
+        if (npos != pos) {
+            lds_barrier();
+            nchunks = chunks(npos);
+        }
+        pos = npos;
+        chunk = nchunk;
+        return false;
+    };
+    while (!step(A, B) && !step(B, A)) {}
+    if (!P.tail) lds_barrier();
+
+    // the tile's own rows
+    const float rn = recip(P.n);
+    for (int e = tid; e < bxe * P.n * P.m * K; e += nt) {
+        const int t = e / K, line = small_div(t, rbx), ii = t - line * bxe;
+        const int kq = small_div(line, rn), jq = line - kq * P.n, jj = J0 + jq, kk = K0 + kq;
+        const int cell = 1 + ii + P.sx * ((jq - P.hj) + P.pj * (kq - P.hk));
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int bx = ext_x(c), by = ext_y(c);
+            if (ii < bx && jj < by && kk < ext_z(c))
+                zout[(i64)(P.off[c] + ii + bx * (jj + by * kk)) * K + rhs] = zs[(cell + c * block) * K + rhs];
+        }
+    }
+}
+
+namespace {
+
+struct Box {  // [jlo, jhi) x [klo, khi) in cells
+    int jlo, jhi, klo, khi;
+    void add(const Box &b)
+    {
+        jlo = std::min(jlo, b.jlo); jhi = std::max(jhi, b.jhi);
+        klo = std::min(klo, b.klo); khi = std::max(khi, b.khi);
+    }
+};
+
+// The colour-(c ^ f) cells next to the colour-c cells of b: an even line's
+// neighbours are the odd lines of the cell before and of its own, an odd
+// line's the even lines of its own cell and of the one after.
+Box reach(const Box &b, int c, int f)
+{
+    Box o = b;
+    if (f & 2) { if (c & 2) ++o.jhi; else --o.jlo; }
+    if (f & 4) { if (c & 4) --o.klo; else ++o.khi; }  // colours 4-7 lie on the even planes
+    return o;
+}
+
+// Fills P for tiles of n x m cells; returns the LDS cells a workgroup needs.
+i64 sweep_args(SweepArgs &P, const Geom &g, const Geom *gc, int n, int m, bool forward, bool zero, bool skip_first,
+               int tail)
+{
+    const Box own{0, n, 0, m};
+    Box need[8];
+    auto pos = [&](int c) { return forward ? c : 7 - c; };
+    auto flips = [&](unsigned mask) {
+        unsigned b = 0;
+        for (int s = 0; s < kSlots; ++s)
+            if (mask >> s & 1u) b |= 1u << (slot_flip(s) - 1);
+        return b;
+    };
+    const unsigned tailmask = tail == 1 ? kAllSlots & ~zero_guess_mask(4, forward) : kAllSlots;
+    for (Box &b : need) b = own;
+    if (tail)
+        for (int f = 1; f < 8; ++f)
+            if (flips(tailmask) >> (f - 1) & 1u) need[4 ^ f].add(reach(own, 4, f));
+    // a row relaxed at a position needs the new values of every earlier colour next to it
+    for (int q = 7; q >= 0; --q) {
+        const int c = forward ? q : 7 - q;
+        for (int f = 1; f < 8; ++f)
+            if (pos(c ^ f) < q) need[c ^ f].add(reach(need[c], c, f));
+    }
+    // held: these, and what a row next to them reads (zeros, in a sweep from zero)
+    Box held = own;
+    for (int c = 0; c < 8; ++c) {
+        held.add(need[c]);
+        for (int f = 1; f < 8; ++f) held.add(reach(need[c], c, f));
+    }
+    for (int q = 0; q < 9; ++q) {
+        const int c = q == 8 ? 4 : forward ? q : 7 - q;
+        const Box &b = q == 8 ? own : need[c];
+        P.pos[q] = pack_pos(b.jlo, b.jhi - b.jlo, b.klo, b.khi - b.klo,
+                            flips(q == 8 ? tailmask : zero ? zero_guess_mask(c, forward) : kAllSlots));
+    }
+    for (int c = 0; c < 8; ++c) P.off[c] = (int)g.off[c];
+    P.nx1 = g.nx + 1; P.ny1 = g.ny + 1; P.nz1 = g.nz + 1;
+    P.n = n; P.m = m;
+    P.tj = ((g.ny + 1) / 2 + n - 1) / n;
+    P.forward = forward;
+    P.first = skip_first ? 1 : 0;
+    P.tail = tail;
+    P.sx = (g.nx + 1) / 2 + 1;
+    P.hj = held.jlo; P.pj = held.jhi - held.jlo;
+    P.hk = held.klo; P.pk = held.khi - held.klo;
+    if (gc) {
+        for (int c = 0; c < 8; ++c) P.coff[c] = (int)gc->off[c];
+        P.cnx1 = gc->nx + 1; P.cny1 = gc->ny + 1;
+    }
+    return 1 + (i64)8 * P.sx * P.pj * P.pk;
+}
+
+int sweep_tiles(const Geom &g, int n, int m)
+{
+    return (((g.ny + 1) / 2 + n - 1) / n) * (((g.nz + 1) / 2 + m - 1) / m);
+}
+
+// Lanes at work at position q, of the arguments P for tiles of one cell, when
+// the tiles have n x m cells (every box grows with its tile).
+i64 sweep_lanes(const SweepArgs &P, int q, int n, int m, int K)
+{
+    return (i64)(P.nx1 >> 1) * ((P.pos[q] >> 4 & 31) - 1 + n) * ((P.pos[q] >> 13 & 31) - 1 + m) * K;
+}
+
+// The tile whose workgroups, taken one per CU, have the fewest row chunks to
+// work through one after the other; of equal ones the smallest.  Returns the
+// LDS bytes of a workgroup.
+size_t choose_tile(const Geom &g, const SweepArgs &P, int K, size_t vb, int &n, int &m)
+{
+    i64 best = -1;
+    size_t lds = 0;
+    for (int mm = 1; mm <= 8; ++mm)
+        for (int nn = 1; nn <= 8; ++nn) {
+            const i64 cells = 1 + (i64)8 * P.sx * (P.pj - 1 + nn) * (P.pk - 1 + mm);
+            const size_t b = ((size_t)cells * K * vb + 15) / 16 * 16;
+            if (b > kSweepLds) break;
+            i64 items = 0;
+            for (int q = P.first; q < 8; ++q) items += (sweep_lanes(P, q, nn, mm, K) + kSweepThreads - 1) / kSweepThreads;
+            const i64 cost = (sweep_tiles(g, nn, mm) + kCus - 1) / kCus * items;
+            if (best < 0 || cost < best) { best = cost; n = nn; m = mm; lds = b; }
+        }
+    return lds;
+}
+
+template <typename V, typename S, int K>
+void sweep_launch(const V *v, const V *d, const SweepArgs &P, int tiles, int threads, size_t lds, const void *r,
+                  const void *zin, const void *zc, void *zout, void *rc, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_sweep<V, S, K>), dim3(tiles), dim3(threads), lds, s, P, v, d, (const S *)r, (const S *)zin,
+                       (const S *)zc, (S *)zout, (S *)rc);
+}
+
+}  // namespace
+
+bool sweep_possible(const Matrix &A, int K, Prec p)
+{
+    const Geom &g = A.g;
+    SweepArgs P;
+    return A.clog2 == kDefaultEllChunkLog2 && g.N * K < (1 << 24) &&
+           sweep_args(P, g, nullptr, 1, 1, true, false, false, 2) * K * (i64)vec_bytes(p) <= (i64)kSweepLds - 16;
+}
+
+void launch_sweep(const Matrix &A, Prec p, int K, bool forward, bool skip_first, const void *r, const void *zin,
+                  const Geom *gc, const void *zc, void *zout, void *rc, hipStream_t s)
+{
+    if (!sweep_possible(A, K, p)) throw std::runtime_error("launch_sweep: level too large");
+    const bool zero = zin == nullptr;
+    const int tail = !rc ? 0 : zero ? 1 : 2;
+    const Geom &g = A.g;
+    SweepArgs one{}, P{};
+    sweep_args(one, g, gc, 1, 1, forward, zero, skip_first, tail);
+    int n = 1, m = 1;
+    const size_t lds = choose_tile(g, one, K, vec_bytes(p), n, m);
+    sweep_args(P, g, gc, n, m, forward, zero, skip_first, tail);
+    P.remap = tile_remap(A);
+    i64 lanes = 64;
+    for (int q = P.first; q < 8; ++q) lanes = std::max(lanes, sweep_lanes(one, q, n, m, K));
+    const int threads = (int)std::min<i64>(kSweepThreads, (lanes + 63) / 64 * 64);
+    const int tiles = sweep_tiles(g, n, m);
+    auto go = [&](auto *v, auto *d, auto sv) {
+        using V = std::remove_const_t<std::remove_pointer_t<decltype(v)>>;
+        using S = decltype(sv);
+        if (K == 1) sweep_launch<V, S, 1>(v, d, P, tiles, threads, lds, r, zin, zc, zout, rc, s);
+        else if constexpr (!std::is_same<S, __half>::value && !std::is_same<S, bf16>::value) {
+            if (K == 2) sweep_launch<V, S, 2>(v, d, P, tiles, threads, lds, r, zin, zc, zout, rc, s);
+            else if (K == 4) sweep_launch<V, S, 4>(v, d, P, tiles, threads, lds, r, zin, zc, zout, rc, s);
+            else if (K == 8) sweep_launch<V, S, 8>(v, d, P, tiles, threads, lds, r, zin, zc, zout, rc, s);
+            else throw std::runtime_error("launch_sweep: unsupported batch width");
+        } else throw std::runtime_error("launch_sweep: no batches of the 16-bit hierarchy");
+    };
+    switch (p) {
+    case P64: go(A.v64, A.d64, double{}); break;
+    case P32: go(A.v32, A.d32, float{}); break;
+    case P16: go(A.v16, A.d16, float{}); break;
+    case PB16: go(A.vb16, A.db16, float{}); break;
+    case P16V: go(A.v16, A.d16, __half{}); break;
+    case PB16V: go(A.vb16, A.db16, bf16{}); break;
+    }
+    HPGMX_LAUNCH_CHECK();
+}
+
+}  // namespace hpgmx

@@ -1,0 +1,95 @@
+"""Half-sweeps run as one launch (tiles of whole x-lines with halo rows relaxed redundantly) against the colour
+launches: the same operations in the same order, so the results must agree bit for bit (tolerance zero).  A handle
+with pair_rows = 0 runs every colour as its own launch."""
+import numpy as np
+import pytest
+
+from paper_2507_11512_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+VEC = {0: "float64", 4: "float16", 5: "bfloat16"}
+
+
+@pytest.fixture(scope="module")
+def hp():
+    from paper_2507_11512_amd import hpgmx
+    return hpgmx
+
+
+def vec(dims, seed, dtype):
+    import torch
+    return torch.from_numpy(inputs.uniform(dims, seed)).to("cuda", getattr(torch, VEC.get(dtype, "float32")))
+
+
+def pair(hp, dims, **kw):
+    return [hp.Problem(dims, beta=0.3, layout=lay, **kw) for lay in (None, {"pair_rows": 0})]
+
+
+# tile edges: one cell, fewer cells than a tile, odd extents in each direction, several tiles with a remainder, the
+# largest FP32 level, long and short x-lines
+DIMS = [(2, 2, 2), (3, 5, 4), (13, 9, 7), (2, 34, 3), (64, 3, 2), (37, 26, 51), (50, 38, 26), (100, 102, 102)]
+
+
+@pytest.mark.parametrize("dims", DIMS)
+@pytest.mark.parametrize("dtype", [0, 1, 2, 3, 4, 5])
+def test_smooth(hp, dims, dtype):
+    import torch
+    Ps = pair(hp, dims, levels=1)
+    try:
+        r = vec(dims, 41, dtype)
+        for sweep in (0, 1, 2):
+            for zero in (True, False):
+                zs = [vec(dims, 42, dtype) for _ in Ps]
+                for P, z in zip(Ps, zs):
+                    hp.smooth(P.h, 0, dtype, sweep, r, z, zero_guess=zero)
+                assert torch.equal(zs[0], zs[1]), (sweep, zero)
+    finally:
+        for P in Ps:
+            P.close()
+
+
+@pytest.mark.parametrize("dims,levels,pre,post,coarsest", [((16, 16, 16), 3, 1, 1, 1), ((24, 20, 28), 3, 1, 1, 1),
+                                                           ((50, 38, 26), 2, 2, 1, 1), ((48, 8, 40), 3, 1, 2, 3),
+                                                           ((32, 24, 16), 3, 2, 2, 1), ((16, 16, 16), 2, 0, 1, 1),
+                                                           ((16, 16, 16), 2, 1, 0, 0), ((192, 160, 128), 4, 1, 1, 1)])
+@pytest.mark.parametrize("dtype,cols", [(0, "int32"), (1, "int32"), (1, "offset16"), (2, "int32"), (5, "int32")])
+def test_vcycle(hp, dims, levels, pre, post, coarsest, dtype, cols):
+    """Restriction and prolongation ride on the sweeps; every sweep kind, several sweeps per level."""
+    import torch
+    for sweep in ("forward", "backward", "symmetric"):
+        Ps = pair(hp, dims, levels=levels, pre=pre, post=post, coarsest=coarsest, sweep=sweep, cols=cols)
+        try:
+            r = vec(dims, 43, dtype)
+            zs = [torch.full_like(r, float("nan")) for _ in Ps]
+            for P, z in zip(Ps, zs):
+                hp.vcycle(P.h, dtype, r, z)
+            assert torch.isfinite(zs[0]).all() and torch.equal(zs[0], zs[1]), sweep
+        finally:
+            for P in Ps:
+                P.close()
+
+
+@pytest.mark.parametrize("bound", [False, True])
+def test_solve_in_bound_workspace(hp, bound):
+    """The second vectors of the tiled sweeps come out of a workspace of the advertised size; replayed graphs and
+    launches from the host give the same iterates."""
+    import torch
+    dims = (40, 24, 32)
+    out = []
+    for graph in (False, True):
+        ws = None
+        if bound:
+            h = hp.setup_problem(*dims, beta=0.3)
+            ws = torch.empty(hp.workspace_bytes(h, levels=3, restart=30, dtype_mask=3), dtype=torch.uint8, device="cuda")
+            hp.destroy(h)
+        P = hp.Problem(dims, beta=0.3, levels=3, sweep="symmetric", workspace=ws)
+        b = P.rhs_from_x(vec(dims, 44, 0))
+        for _ in range(3):
+            x, st = P.solve(b, tol=1e-11, precision="mxp", graph=graph)
+            assert st.converged
+            out.append(x.cpu().numpy())
+        P.close()
+    assert all(np.array_equal(out[0], o) for o in out[1:])
+    ref = inputs.uniform(dims, 44)
+    assert np.linalg.norm(out[0] - ref) <= 1e-8 * np.linalg.norm(ref)
