@@ -71,6 +71,7 @@ struct BatchTune {
     int R[HPGMX_BK_COUNT][kMaxLevels] = {};
     double ms[HPGMX_BK_COUNT][kMaxLevels] = {};
     bool set = false;
+    bool given = false;  // by hpgmx_batch_set_tuning: these tiles are launched
 };
 
 // State of batched solves with K interleaved right-hand sides.  Vectors are
@@ -322,13 +323,18 @@ void zero_entry(hpgmx_ctx *c, void *v, i64 N, Prec p)
 // colour launches and with tiles on level 0 too, 4457 and 3204 us at 24^3,
 // 5467 and 4205 at 64^3 and 7561 and 6238 at 96^3 in FP32 (0.9M rows), 6391
 // and 4788 at 64^3, 7593 and 7070 at 80^3 (0.5M) and 10170 either way at
-// 96^3 in FP64, where a 96 x 88 x 80 level in tiles lost 2 %.  A handle
+// 96^3 in FP64, where a 96 x 88 x 80 level in tiles lost 2 %.  Batches gain
+// over the same range (30 steps, 3 levels, colour launches and tiles: FP32
+// 2 x 32^3 6011 and 3633 us, 4 x 48^3 7084 and 5224, 8 x 48^3 8226 and 7643;
+// FP64 4 x 48^3 8761 and 7061), but with 16-bit matrices, whose vectors are
+// FP32, up to half the rows of an FP32 batch: 4 x 48^3 6756 and 5668, 8 x
+// 48^3 7789 and 8605.  A handle
 // with a pair_rows of its own gets the launches it asks for, and a profiled
 // solve the launches that are timed one by one.
 constexpr i64 kSweepBytes = 1 << 22;
 bool tiled_size(const Layout &lay, i64 N, int K, Prec p)
 {
-    const i64 vb = matrix_prec(p) == P64 ? 8 : matrix_prec(p) == P32 ? 4 : 2;
+    const i64 vb = matrix_prec(p) == P64 ? 8 : matrix_prec(p) == P32 ? 4 : K > 1 ? 8 : 2;
     return lay.pair_rows == kDefaultPairRows && N * K * vb <= kSweepBytes;
 }
 bool tiled(const hpgmx_ctx *c, int l, Prec p, int K)
@@ -970,6 +976,8 @@ void ensure_batch_prec(hpgmx_ctx *c, Batch &B, Prec p, int m)
             B.lr[vt][l] = gathered_batch(c, c->lv[l].A.g.N, K, p);
             B.lz[vt][l] = gathered_batch(c, c->lv[l].A.g.N, K, p);
         }
+        const size_t b = (size_t)c->lv[l].A.g.N * K * vec_bytes(p);
+        if (!B.lz2[vt][l] && tiled_size(c->layout, c->lv[l].A.g.N, K, p) && c->fits(b)) B.lz2[vt][l] = c->dalloc(b);
     }
     if (m <= 0) return;
     const i64 N0 = c->lv[0].A.g.N;
@@ -1064,11 +1072,30 @@ void bpresmooth_restrict(hpgmx_ctx *c, Batch &B, int l, Prec p, int kind, int ns
         launch_brestrict(c->lv[l].A, gc, p, B.K, R, r, z, rc, c->stream);
 }
 
-// The V-cycle of vcycle() for K right-hand sides at once (out: as vcycle()).
-void bvcycle(hpgmx_ctx *c, Batch &B, int l, Prec p, const void *r, void *z, BSpmvOut out = {})
+// tiled() for a batch: a table of tile shapes set by the caller asks for the
+// colour launches it describes.
+bool btiled(const hpgmx_ctx *c, const Batch &B, int l, Prec p)
+{
+    const BatchTune &t = B.tune[p];
+    return tiled(c, l, p, B.K) && !(t.given && (t.R[HPGMX_BK_GS][l] || t.R[HPGMX_BK_GS_ZERO][l]));
+}
+bool btiled_level(const hpgmx_ctx *c, const Batch &B, int l, Prec p, const void *z2)
+{
+    return tiled_level(c, l, p, B.K, z2) && btiled(c, B, l, p);
+}
+
+// The V-cycle of vcycle() for K right-hand sides at once (out, z2: as vcycle()).
+void bvcycle(hpgmx_ctx *c, Batch &B, int l, Prec p, const void *r, void *z, BSpmvOut out = {}, void *z2 = nullptr)
 {
     const hpgmx_mg_desc &mg = c->mg;
     const int vt = vt_of(p);
+    if (l > 0) z2 = B.lz2[vt][l];
+    if (!out.y && !out.part && btiled_level(c, B, l, p, z2)) {
+        const bool leaf = l == mg.levels - 1;
+        tiled_vcycle(c, l, p, B.K, r, z, z2, leaf ? nullptr : B.lr[vt][l + 1], leaf ? nullptr : B.lz[vt][l + 1],
+                     [&]() { bvcycle(c, B, l + 1, p, B.lr[vt][l + 1], B.lz[vt][l + 1]); });
+        return;
+    }
     if (l == mg.levels - 1) {
         bsmooth_level(c, B, l, p, mg.sweep, r, z, true, mg.coarsest_sweeps);
         return;
@@ -1264,11 +1291,12 @@ hpgmx_status bsolve(hpgmx_ctx *c, int nrhs, const double *Bn, double *Xn, const 
                     // (FP32 and FP64 batches; the last colour alone is not
                     // offered: kSpmvLast runs as kSpmvPlain)
                     const int fc = fused_spmv_colour(c);
-                    const int sm = fc < 0 || (p != P32 && p != P64) || c->spmv_mode == kSpmvLast ? kSpmvPlain
-                                                                                                  : c->spmv_mode;
+                    int sm = fc < 0 || (p != P32 && p != P64) || c->spmv_mode == kSpmvLast ? kSpmvPlain
+                                                                                            : c->spmv_mode;
+                    if (sm == kSpmvSplit && btiled_level(c, B, 0, p, Kr.part)) sm = kSpmvSplitSeparate;
                     BSpmvOut out{};
                     if (sm == kSpmvSplit) { out.y = col(k + 1); out.ctrl = B.ctrl; out.k = k; out.part = Kr.part; }
-                    bvcycle(c, B, 0, p, col(k), Kr.z, out);
+                    bvcycle(c, B, 0, p, col(k), Kr.z, out, Kr.part);
                     {
                         ProfScope ps(c, HPGMX_K_SPMV, 0);
                         const int Rs = tile_r(c, B, p, HPGMX_BK_SPMV, 0);
@@ -1345,7 +1373,7 @@ hpgmx_status bsolve(hpgmx_ctx *c, int nrhs, const double *Bn, double *Xn, const 
                 ProfScope ps(c, HPGMX_K_GEMV, 0);
                 launch_gemv(M, K, p, Kr.Q, ldq, kmax, B.ctrl, Kr.u, c->stream);
             }
-            bvcycle(c, B, 0, p, Kr.u, Kr.z);
+            bvcycle(c, B, 0, p, Kr.u, Kr.z, {}, Kr.part);
             {
                 ProfScope ps(c, HPGMX_K_UPDATE, 0);
                 launch_update(M, p, Kr.z, B.x, c->stream);
@@ -1395,6 +1423,10 @@ size_t plan_batch_bytes(const hpgmx_problem_desc &pd, const hpgmx_mg_desc &mg, i
             const size_t N = (size_t)nx * ny * nz;
             add((N + 1) * K * vb);
             add((N + 1) * K * vb);
+            bool second = false;  // the tiled sweeps' second z
+            for (int p = 0; p < 4; ++p)
+                second = second || (((mask >> p) & 1u) && vt_of((Prec)p) == vt && tiled_size(lay, (i64)N, K, (Prec)p));
+            if (second) add(N * K * vb);
             nx /= 2; ny /= 2; nz /= 2;
         }
         add((size_t)krylov_ldq((i64)(N0 * K), lay.ldq_pad) * (m + 1) * vb);
@@ -1953,7 +1985,7 @@ hpgmx_status hpgmx_batch_set_tuning(hpgmx_handle h, int nrhs, int dtype, const h
                 T.R[k][l] = in->rhs_per_lane[k][l];
                 T.ms[k][l] = in->ms[k][l];
             }
-        T.set = true;
+        T.set = T.given = true;
         B.tune[p] = T;
         h->drop_graphs();
         return HPGMX_OK;
@@ -2017,8 +2049,16 @@ hpgmx_status hpgmx_smooth_batched(hpgmx_handle h, int level, int dtype, int swee
         zero_batch_row(h, B.tmp[vt][1], A.g.N, K, p);
         launch_bnat2int(A.g, p, p, K, nrhs, R, B.tmp[vt][0], h->stream);
         if (!zero_guess) launch_bnat2int(A.g, p, p, K, nrhs, Z, B.tmp[vt][1], h->stream);
-        bsmooth_level(h, B, level, p, sweep, B.tmp[vt][0], B.tmp[vt][1], zero_guess != 0, 1);
-        launch_bint2nat(A.g, p, p, K, nrhs, B.tmp[vt][1], Z, h->stream);
+        void *out = B.tmp[vt][1];
+        if (btiled(h, B, level, p)) {
+            void *other = B.tmp[vt][2];
+            if (half_sweeps(sweep, 1) & 1) std::swap(out, other);
+            tiled_sweeps(h, level, p, K, sweep, 1, B.tmp[vt][0], zero_guess ? nullptr : B.tmp[vt][1], out, other,
+                         nullptr, nullptr);
+        } else {
+            bsmooth_level(h, B, level, p, sweep, B.tmp[vt][0], out, zero_guess != 0, 1);
+        }
+        launch_bint2nat(A.g, p, p, K, nrhs, out, Z, h->stream);
         return HPGMX_OK;
     });
 }
@@ -2068,7 +2108,7 @@ hpgmx_status hpgmx_vcycle_batched(hpgmx_handle h, int dtype, int nrhs, const voi
         const Matrix &A = h->lv[0].A;
         zero_batch_row(h, B.tmp[vt][1], A.g.N, K, p);
         launch_bnat2int(A.g, p, p, K, nrhs, R, B.tmp[vt][0], h->stream);
-        bvcycle(h, B, 0, p, B.tmp[vt][0], B.tmp[vt][1]);
+        bvcycle(h, B, 0, p, B.tmp[vt][0], B.tmp[vt][1], {}, B.tmp[vt][2]);
         launch_bint2nat(A.g, p, p, K, nrhs, B.tmp[vt][1], Z, h->stream);
         return HPGMX_OK;
     });

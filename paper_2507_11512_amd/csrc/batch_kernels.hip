@@ -106,6 +106,27 @@ __global__ __launch_bounds__(kBlock) void k_bspmv_colour(i64 row0, i64 cnt, i64 
     stp_stream<T, R>(y + o, out);
 }
 
+// All rows of every colour in one launch (see k_spmv_split in
+// stencil_kernels.hip), one right-hand side per lane.
+template <typename V, int K>
+__global__ __launch_bounds__(kBlock) void k_bspmv_split(Geom gm, EarlySlots es, int clog2, int remap,
+                                                        const V *__restrict__ offv, const int *__restrict__ offc,
+                                                        const V *__restrict__ diag,
+                                                        const typename VecT<V>::T *__restrict__ x,
+                                                        typename VecT<V>::T *__restrict__ y, const Ctrl *ctrl, int k)
+{
+    using T = typename VecT<V>::T;
+    const i64 t = gtid_xcd(remap), p = t / K;
+    if (p >= gm.N) return;
+    const int j = (int)(t % K);
+    const EllRow er = ell_row(p, gm.N, clog2);
+    const T d = to_t<T>(diag[p]), xp = x[t];
+    const unsigned early = es.of(row_colour(gm, p));
+    T se;
+    const T sl = ell_row_dot_split<T, V, false, K>(offv, offc, x + j, er, p, nullptr, gm.N, early, se);
+    y[t] = spmv_row_value<T>(d, xp, se + sl, ctrl ? ctrl[j].colscale + k : nullptr);
+}
+
 // ---- Gauss-Seidel, one colour (rows [row0, row0 + cnt)) ------------------------------------
 // WOUT as in k_gs (stencil_kernels.hip): the last sweep of a V-cycle's
 // level-0 post-smoothing also writes the SpMV rows of its last colour
@@ -375,8 +396,15 @@ void launch_bspmv_split(const Matrix &A, Prec p, int K, int R, const void *x, vo
         using V = std::remove_const_t<std::remove_pointer_t<decltype(v)>>;
         using T = typename VecT<V>::T;
         if constexpr (std::is_same<V, float>::value || std::is_same<V, double>::value) {
-            with_kr(K, R, [&](auto kc, auto rc) {
+            with_kr(K, !fused && A.g.N * K <= kSpmvOneLaunch ? 1 : R, [&](auto kc, auto rc) {
                 constexpr int KK = decltype(kc)::value, RR = decltype(rc)::value;
+                if (!fused && A.g.N * K <= kSpmvOneLaunch) {
+                    if constexpr (RR == 1)
+                        hipLaunchKernelGGL((k_bspmv_split<V, KK>), dim3(lanes_grid(A.g.N, KK, 1)), dim3(kBlock), 0, s,
+                                           A.g, early_slots(forward), A.clog2, tile_remap(A), (const V *)v,
+                                           (const int *)A.col, (const V *)d, (const T *)x, (T *)y, ctrl, k);
+                    return;
+                }
                 // sweep positions 0 and 1 (and 7 when it is not fused): whole rows;
                 // the colour pair in the plane-interleaved order where it applies
                 const int pair_order = A.order >= kRemapSlab && plane_order(A) == kRemapPlanes

@@ -314,13 +314,6 @@ void launch_spmv(const Matrix &A, Prec p, const void *x, void *y, hipStream_t s,
     HPGMX_LAUNCH_CHECK();
 }
 
-// Largest level whose split sums are formed in one launch (k_spmv_split)
-// rather than in a launch per colour: up to the largest level whose sweeps
-// run in tiles.  It reads what the colour launches read; a 30-step cycle
-// takes 3204 instead of 3843 us at 24^3 and 6238 instead of 6675 at 96^3
-// in FP32.
-constexpr i64 kSpmvOneLaunch = 1 << 21;
-
 // ---- SpMV after the last sweep of a V-cycle ---------------------------------------------------
 // In sweep order, the colours at positions 2-6 (forward: 2 ... 6; backward:
 // 5 ... 1) have their row sums split in two: E, the slots to the colours
@@ -385,9 +378,6 @@ static void spmv_colour_launch(const Matrix &A, const V *v, const V *d, const vo
 
 // All rows of every colour in one launch, each row's sum split as above: for
 // the levels where the launches per colour are bound by latency.
-struct EarlySlots {
-    unsigned m[8];  // E per colour; none for the whole rows
-};
 template <typename V, typename S, bool C16>
 __global__ __launch_bounds__(kBlock) void k_spmv_split(Geom g, EarlySlots es, int clog2, int remap,
                                                        const V *__restrict__ offv, const void *__restrict__ offc,
@@ -403,9 +393,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_split(Geom g, EarlySlots es, in
     const EllRow er = ell_row(p, N, clog2);
     const T d = to_t<T>(diag[p]), xp = to_t<T>(x[p]);
     const int c = row_colour(g, p);
-    unsigned early = es.m[0];
-#pragma unroll
-    for (int q = 1; q < 8; ++q) early = c == q ? es.m[q] : early;
+    const unsigned early = es.of(c);
     T se;
     const T sl = ell_row_dot_split<T, V, C16>(offv, offc, x, er, p, C16 ? cm + c * kSlots : nullptr, N, early, se);
     y[p] = spmv_row_value<T>(d, xp, se + sl, scale);
@@ -437,10 +425,8 @@ void launch_spmv_split(const Matrix &A, Prec p, const void *x, void *y, const vo
         with_cols(A, [&](auto c16) {
             constexpr bool C = decltype(c16)::value;
             if (!fused && A.g.N <= kSpmvOneLaunch) {
-                EarlySlots es{};
-                for (int q = 2; q < 7; ++q) es.m[forward ? q : 7 - q] = zero_guess_mask(forward ? q : 7 - q, forward);
-                hipLaunchKernelGGL((k_spmv_split<V, S, C>), dim3(grid_for(A.g.N)), dim3(kBlock), 0, s, A.g, es,
-                                   A.clog2, tile_remap(A), (const V *)v, (const void *)A.col, A.cmap, (const V *)d,
+                hipLaunchKernelGGL((k_spmv_split<V, S, C>), dim3(grid_for(A.g.N)), dim3(kBlock), 0, s, A.g,
+                                   early_slots(forward), A.clog2, tile_remap(A), (const V *)v, (const void *)A.col, A.cmap, (const V *)d,
                                    (const S *)x, (T *)y, scale);
                 return;
             }

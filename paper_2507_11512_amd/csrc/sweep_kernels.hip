@@ -18,13 +18,16 @@
 // memory round trips (the row's entries, then its neighbours) and a kernel
 // boundary, 3-6 us whatever the row count; here the entries of the next
 // colour's rows, which depend on no z, are loaded while the current colour
-// is relaxed, the neighbours come from LDS, and a colour takes about 0.8 us
-// (issue of the row's 26 loads, 26 LDS reads and 26 dependent FMAs).  The
-// price is the halo (1.5 to 4 times the rows).  Measured, FP32 forward, the
-// eight launches with their gaps against this one: 64^3 level 45 -> 12 us
-// from zero with the restriction, 14 us with the prolongation; 32^3 36 ->
-// 11; 16^3 27 -> 9.  Solves of 16^3 (symmetric) 6.5 -> 3.6 ms, 48 x 40 x 32
-// 9.9 -> 5.5 ms, 128^3 63 -> 52.5 ms.
+// is relaxed, the neighbours come from LDS, and a colour takes 0.6-0.8 us
+// (the issue of its instructions: finding the row, 26 loads, 26 LDS reads
+// and 26 dependent FMAs).  The price is the halo (1.5 to 4 times the rows).
+// Measured, FP32 forward, the eight launches with their gaps against this
+// one: 64^3 level 45 -> 12 us from zero with the restriction, 13.6 us with
+// the prolongation; 32^3 36 -> 10; 16^3 27 -> 8.  Solves of 16^3
+// (symmetric) 6.5 -> 3.4 ms, 48 x 40 x 32 9.9 -> 5.4 ms, 128^3 63 -> 52 ms.
+// Slower variants: columns loaded and mapped to LDS cells (18 us on every
+// size), scalar loads of each position's constants (+0.4 us a colour), half
+// of the waves loading while the other half relaxes (+20 %).
 //
 // The tile's z lies in LDS with the same strides for every colour, each line
 // followed by a zero cell and the lines outside the grid zero, so a
@@ -42,7 +45,7 @@ namespace hpgmx {
 
 constexpr int kSweepThreads = 512;        // at most; two waves per SIMD, 256 VGPRs each
 constexpr int kCus = 256;
-constexpr size_t kSweepLds = 64 * 1024;   // bytes of z a workgroup may hold
+constexpr size_t kSweepLds = 144 * 1024;  // bytes of z a workgroup may hold (of the CU's 160 KiB)
 
 // A launch's tiles.  Boxes are in cells, relative to the tile's first cell,
 // and not clipped to the grid.
@@ -57,6 +60,7 @@ struct SweepArgs {
     int remap, forward;
     int first, tail;       // first sweep position; 0, or the restriction after the sweep: 1 from the slots to
                            // colours relaxed after colour 4, 2 r - A z
+    unsigned bytes;        // of the off-diagonal values
     int sx, pj, pk;        // cells per line (the zero included), lines per plane and planes held per colour
     int hj, hk;            // the held box's first line and plane
     int coff[8], cnx1, cny1;  // the coarse level (restriction, prolongation)
@@ -81,20 +85,42 @@ __device__ __forceinline__ void lds_barrier()
 __device__ __forceinline__ int small_div(int t, float rd) { return (int)(((float)t + 0.5f) * rd); }
 __device__ __forceinline__ float recip(int d) { return __builtin_amdgcn_rcpf((float)d); }
 
-// Element `soff + e` (soff the same for every lane) of an array below 2^32 bytes.
-template <typename E> __device__ __forceinline__ E ld_at(const void *base, unsigned soff, unsigned e)
-{
-    const char *b = static_cast<const char *>(base) + soff * sizeof(E);
-    return *reinterpret_cast<const E *>(b + e * (unsigned)sizeof(E));
-}
+// The off-diagonal values through a buffer resource: a load takes a 32-bit
+// offset per lane, the slot's place in a scalar register and an immediate,
+// with no address arithmetic of its own, and a lane past the end reads 0.
+template <typename V> struct SlotLoads {
+    static constexpr int kStride = (int)sizeof(V) << kDefaultEllChunkLog2;  // bytes from slot to slot
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ __forceinline__ SlotLoads(const V *v, unsigned bytes)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<V *>(v), 0, (int)bytes, 0x00027000)) {}
+    __device__ __forceinline__ V at(int s, unsigned off) const
+    {
+        const int imm = s * kStride % 4096, base = s * kStride - imm;
+        if constexpr (sizeof(V) == 8) {
+            typedef unsigned u2 __attribute__((ext_vector_type(2)));
+            const u2 w = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)(off + imm), base, 0);
+            return __builtin_bit_cast(V, w);
+        } else if constexpr (sizeof(V) == 4) {
+            return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)(off + imm), base, 0));
+        } else {
+            return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)(off + imm), base, 0));
+        }
+    }
+};
 
 // Internal index of coarse point (I, J, K).
 __device__ __forceinline__ int coarse_index(const SweepArgs &P, int I, int J, int K)
 {
     const int c = colour_of(I, J, K);
-    int off = P.coff[0];
+    int o[8];
 #pragma unroll
-    for (int q = 1; q < 8; ++q) off = c == q ? P.coff[q] : off;
+    for (int q = 0; q < 8; ++q) {
+        o[q] = P.coff[q];
+        asm("" : "+s"(o[q]));  // select among eight registers, not among addresses to load from
+    }
+    int off = o[0];
+#pragma unroll
+    for (int q = 1; q < 8; ++q) off = c == q ? o[q] : off;
     const int bx = (P.cnx1 - (I & 1)) >> 1, by = (P.cny1 - (J & 1)) >> 1;
     return off + (I >> 1) + bx * ((J >> 1) + by * (K >> 1));
 }
@@ -141,30 +167,43 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(const SweepArgs P, cons
     auto ext_y = [&](int c) { return (P.ny1 - ((c >> 1) & 1)) >> 1; };
     auto ext_z = [&](int c) { return (P.nz1 - (((c >> 2) & 1) ^ 1)) >> 1; };
 
+    // lane q holds position q's word, lane 16 + c colour c's first row: read
+    // from there, not from the arguments, whose scalar loads each position
+    // would wait for
+    const int lane = tid & 63;
+    int table = 0;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) table = lane == q ? (int)P.pos[q] : table;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) table = lane == 16 + c ? P.off[c] : table;
+    auto word = [&](int pos) { return (unsigned)__builtin_amdgcn_readlane(table, pos); };
+    const SlotLoads<V> slots(offv, P.bytes);
+
     // loads this lane's row of chunk `chunk` of position pos
     auto fetch = [&](int pos, int chunk, Row &E) {
-        const unsigned q = P.pos[pos];
+        const unsigned q = word(pos);
         const int c = colour(pos), jn = q >> 4 & 31, jlo = (int)(q & 15) - 8, klo = (int)(q >> 9 & 15) - 8;
         const int kn = q >> 13 & 31;
         const int t = (chunk * nt + tid) / K;
-        const int line = small_div(t, rbx), ii = t - line * bxe;
-        const int kq = small_div(line, recip(jn)), jr = jlo + (line - kq * jn), kr = klo + kq;
+        const int line = small_div(t, rbx), ii = t - __mul24(line, bxe);
+        const int kq = small_div(line, recip(jn)), jr = jlo + (line - __mul24(kq, jn)), kr = klo + kq;
         const int jj = J0 + jr, kk = K0 + kr;
         const int bx = ext_x(c), by = ext_y(c);
-        E.act = kq < kn && ii < bx && (unsigned)jj < (unsigned)by && (unsigned)kk < (unsigned)ext_z(c);
-        E.cell = (1 + c * block + ii + P.sx * ((jr - P.hj) + P.pj * (kr - P.hk))) * K + rhs;
+        E.act = (kq < kn) & (ii < bx) & ((unsigned)jj < (unsigned)by) & ((unsigned)kk < (unsigned)ext_z(c));
+        E.cell = (1 + c * block + ii + __mul24(P.sx, (jr - P.hj) + __mul24(P.pj, kr - P.hk))) * K + rhs;
         E.ii = ii; E.jj = jj; E.kk = kk;
-        if (!E.act) return;
-        const int p = P.off[c] + ii + bx * (jj + by * kk);
+        const int p = E.act ? (int)word(16 + c) + ii + __mul24(bx, jj + __mul24(by, kk)) : 0;
         E.r = r[(i64)p * K + rhs];
         E.d = diag[p];
-        const unsigned e = ((unsigned)p / kChunk) * (kSlots * kChunk) + (unsigned)p % kChunk;
+        const unsigned e = E.act ? ((unsigned)__mul24(p / (int)kChunk, kSlots * kChunk) + (unsigned)p % kChunk) *
+                                       (unsigned)sizeof(V)
+                                 : 0x80000000u;  // past the end
 #pragma unroll
         for (int f = 1; f < 8; ++f) {
             if (q >> (17 + f) & 1u) {
 #pragma unroll
                 for (int s = 0; s < kSlots; ++s)
-                    if (slot_flip(s) == f) E.a[s] = ld_at<V>(offv, s * kChunk, e);
+                    if (slot_flip(s) == f) E.a[s] = slots.at(s, e);
             } else {  // not read: adds 0
 #pragma unroll
                 for (int s = 0; s < kSlots; ++s)
@@ -202,7 +241,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(const SweepArgs P, cons
 
     const int last = P.tail ? 8 : 7;
     auto chunks = [&](int pos) {
-        const unsigned q = P.pos[pos];
+        const unsigned q = word(pos);
         return (bxe * (int)(q >> 4 & 31) * (int)(q >> 13 & 31) * K + nt - 1) / nt;
     };
 
@@ -398,6 +437,9 @@ template <typename V, typename S, int K>
 void sweep_launch(const V *v, const V *d, const SweepArgs &P, int tiles, int threads, size_t lds, const void *r,
                   const void *zin, const void *zc, void *zout, void *rc, hipStream_t s)
 {
+    if (lds > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sweep<V, S, K>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        throw std::runtime_error("launch_sweep: the device refuses the workgroup's LDS");
     hipLaunchKernelGGL((k_sweep<V, S, K>), dim3(tiles), dim3(threads), lds, s, P, v, d, (const S *)r, (const S *)zin,
                        (const S *)zc, (S *)zout, (S *)rc);
 }
@@ -408,7 +450,7 @@ bool sweep_possible(const Matrix &A, int K, Prec p)
 {
     const Geom &g = A.g;
     SweepArgs P;
-    return A.clog2 == kDefaultEllChunkLog2 && g.N * K < (1 << 24) &&
+    return A.clog2 == kDefaultEllChunkLog2 && g.N * K < (1 << 22) &&
            sweep_args(P, g, nullptr, 1, 1, true, false, false, 2) * K * (i64)vec_bytes(p) <= (i64)kSweepLds - 16;
 }
 
@@ -425,6 +467,7 @@ void launch_sweep(const Matrix &A, Prec p, int K, bool forward, bool skip_first,
     const size_t lds = choose_tile(g, one, K, vec_bytes(p), n, m);
     sweep_args(P, g, gc, n, m, forward, zero, skip_first, tail);
     P.remap = tile_remap(A);
+    P.bytes = (unsigned)(ell_entries(g.N, A.clog2) * (i64)(p == P64 ? 8 : p == P32 ? 4 : 2));
     i64 lanes = 64;
     for (int q = P.first; q < 8; ++q) lanes = std::max(lanes, sweep_lanes(one, q, n, m, K));
     const int threads = (int)std::min<i64>(kSweepThreads, (lanes + 63) / 64 * 64);

@@ -13,6 +13,9 @@ VEC = {0: "float64", 4: "float16", 5: "bfloat16"}
 
 @pytest.fixture(scope="module")
 def hp():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
     from paper_2507_11512_amd import hpgmx
     return hpgmx
 
@@ -65,6 +68,31 @@ def test_vcycle(hp, dims, levels, pre, post, coarsest, dtype, cols):
             for P, z in zip(Ps, zs):
                 hp.vcycle(P.h, dtype, r, z)
             assert torch.isfinite(zs[0]).all() and torch.equal(zs[0], zs[1]), sweep
+        finally:
+            for P in Ps:
+                P.close()
+
+
+# interleaved right-hand sides: levels below and above what a workgroup can hold, odd extents
+@pytest.mark.parametrize("dims,levels", [((16, 12, 20), 3), ((40, 48, 56), 2), ((37, 26, 51), 1), ((64, 40, 48), 3)])
+@pytest.mark.parametrize("nrhs", [2, 3, 8])
+@pytest.mark.parametrize("dtype", [0, 1, 3])
+def test_batched(hp, dims, levels, nrhs, dtype):
+    import torch
+    for sweep in ("forward", "backward", "symmetric"):
+        Ps = pair(hp, dims, levels=levels, sweep=sweep)
+        try:
+            r = torch.stack([vec(dims, 60 + j, dtype) for j in range(nrhs)])
+            zs = [torch.full_like(r, float("nan")) for _ in Ps]
+            for P, z in zip(Ps, zs):
+                hp.vcycle_batched(P.h, dtype, r, z)
+            assert torch.isfinite(zs[0]).all() and torch.equal(zs[0], zs[1]), sweep
+            code = {"forward": hp.GS_FORWARD, "backward": hp.GS_BACKWARD, "symmetric": hp.GS_SYMMETRIC}[sweep]
+            for zero in (True, False):
+                for P, z in zip(Ps, zs):
+                    z.copy_(r)
+                    hp.smooth_batched(P.h, 0, dtype, code, r, z, zero_guess=zero)
+                assert torch.equal(zs[0], zs[1]), (sweep, zero)
         finally:
             for P in Ps:
                 P.close()
