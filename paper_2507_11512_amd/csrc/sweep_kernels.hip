@@ -131,10 +131,16 @@ __host__ __device__ constexpr int slot_flip(int s)
     return ((t % 3 - 1) & 1) | (((t / 3) % 3 - 1) & 1) << 1 | ((t / 9 - 1) & 1) << 2;
 }
 
+// Right-hand sides per lane of a batch of K.  Two share the row's loads and
+// read their neighbours together: 30 steps at 8 x 48^3 in FP32 7619 -> 6654
+// us, 4 x 64^3 6468 -> 6022, FP64 4 x 48^3 6961 -> 6463, and 1-4 % more at
+// 16^3; four lost to two at 8 x 32^3 and by 20 % in FP64.
+template <int K> constexpr int kSweepR = K >= 2 ? 2 : 1;
+
 // One row's entries, loaded ahead of its relaxation.
-template <typename V, typename S> struct SweepRow {
+template <typename V, typename S, int R> struct SweepRow {
     V a[kSlots];
-    S r;
+    Pack<S, R> r;
     V d;
     int cell;         // its own, times K, plus the right-hand side
     int ii, jj, kk;   // in its colour block
@@ -143,20 +149,21 @@ template <typename V, typename S> struct SweepRow {
 
 }  // namespace
 
-// K interleaved right-hand sides, one per lane (K lanes share a row).
-template <typename V, typename S, int K>
+// K interleaved right-hand sides, R per lane (K / R lanes share a row).
+template <typename V, typename S, int K, int R>
 __global__ __launch_bounds__(kSweepThreads) void k_sweep(const SweepArgs P, const V *__restrict__ offv,
                                                          const V *__restrict__ diag, const S *__restrict__ r,
                                                          const S *__restrict__ zin, const S *__restrict__ zc,
                                                          S *__restrict__ zout, S *__restrict__ rc)
 {
     using T = typename VecT<V>::T;
-    using Row = SweepRow<V, S>;
+    using Row = SweepRow<V, S, R>;
+    constexpr int L = K / R;
     constexpr unsigned kChunk = 1u << kDefaultEllChunkLog2;
     extern __shared__ __align__(16) unsigned char smem[];
     S *zs = reinterpret_cast<S *>(smem);
     const int tid = threadIdx.x, nt = blockDim.x;
-    const int rhs = K > 1 ? tid % K : 0;
+    const int rhs = K > 1 ? tid % L * R : 0;
     const int tile = (int)xcd_tile(blockIdx.x, gridDim.x, P.remap);
     const int kt = tile / P.tj, K0 = kt * P.m, J0 = (tile - kt * P.tj) * P.n;
     const int plane = P.sx * P.pj, block = plane * P.pk;  // cells
@@ -184,7 +191,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(const SweepArgs P, cons
         const unsigned q = word(pos);
         const int c = colour(pos), jn = q >> 4 & 31, jlo = (int)(q & 15) - 8, klo = (int)(q >> 9 & 15) - 8;
         const int kn = q >> 13 & 31;
-        const int t = (chunk * nt + tid) / K;
+        const int t = (chunk * nt + tid) / L;
         const int line = small_div(t, rbx), ii = t - __mul24(line, bxe);
         const int kq = small_div(line, recip(jn)), jr = jlo + (line - __mul24(kq, jn)), kr = klo + kq;
         const int jj = J0 + jr, kk = K0 + kr;
@@ -193,7 +200,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(const SweepArgs P, cons
         E.cell = (1 + c * block + ii + __mul24(P.sx, (jr - P.hj) + __mul24(P.pj, kr - P.hk))) * K + rhs;
         E.ii = ii; E.jj = jj; E.kk = kk;
         const int p = E.act ? (int)word(16 + c) + ii + __mul24(bx, jj + __mul24(by, kk)) : 0;
-        E.r = r[(i64)p * K + rhs];
+        E.r = ldp<S, R>(r + ((i64)p * K + rhs));
         E.d = diag[p];
         const unsigned e = E.act ? ((unsigned)__mul24(p / (int)kChunk, kSlots * kChunk) + (unsigned)p % kChunk) *
                                        (unsigned)sizeof(V)
@@ -213,7 +220,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(const SweepArgs P, cons
     };
 
     // sum over the slots of a z, the z gathered from LDS, in slot order
-    auto row_sum = [&](int pos, const Row &E) -> T {
+    auto row_sum = [&](int pos, const Row &E, T (&acc)[R]) {
         const int c = colour(pos);
         // cell of the neighbour minus the row's own: an even line's (or
         // plane's) neighbours are the odd ones of the cell before and of its
@@ -223,26 +230,28 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(const SweepArgs P, cons
                   fz = (c & 4) ? -4 * block : 4 * block;
         const int dy[3] = {fy - (yo ? 0 : P.sx), 0, fy + (yo ? P.sx : 0)};
         const int dz[3] = {fz - (zo ? 0 : plane), 0, fz + (zo ? plane : 0)};
-        S xv[kSlots];
+        Pack<S, R> xv[kSlots];
 #pragma unroll
         for (int g = 0; g < 9; ++g) {  // lines dk, dj
             const int at = E.cell + (dz[g / 3] + dy[g % 3]) * K;
             const S *x = zs + (at + fx * K);
             const int s = 3 * g - (g > 4 ? 1 : 0);  // slot of di = -1
-            xv[s] = x[0];
-            if (g != 4) xv[s + 1] = zs[at];
-            xv[g == 4 ? s + 1 : s + 2] = x[K];
+            xv[s] = ldp<S, R>(x);
+            if (g != 4) xv[s + 1] = ldp<S, R>(zs + at);
+            xv[g == 4 ? s + 1 : s + 2] = ldp<S, R>(x + K);
         }
-        T acc = (T)0;
 #pragma unroll
-        for (int s = 0; s < kSlots; ++s) acc = madd(to_t<T>(E.a[s]), to_t<T>(xv[s]), acc);
-        return acc;
+        for (int i = 0; i < R; ++i) acc[i] = (T)0;
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s)
+#pragma unroll
+            for (int i = 0; i < R; ++i) acc[i] = madd(to_t<T>(E.a[s]), to_t<T>(xv[s].v[i]), acc[i]);
     };
 
     const int last = P.tail ? 8 : 7;
     auto chunks = [&](int pos) {
         const unsigned q = word(pos);
-        return (bxe * (int)(q >> 4 & 31) * (int)(q >> 13 & 31) * K + nt - 1) / nt;
+        return (bxe * (int)(q >> 4 & 31) * (int)(q >> 13 & 31) * L + nt - 1) / nt;
     };
 
     Row A, B;
@@ -254,7 +263,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(const SweepArgs P, cons
         if (tid < K) zs[tid] = from_t<S>((T)0);
         const float rsx = recip(P.sx), rpj = recip(P.pj);
         for (int e = tid; e < block * K; e += nt) {
-            const int t = e / K, line = small_div(t, rsx), ii = t - line * P.sx;
+            const int t = e / K, j = e % K, line = small_div(t, rsx), ii = t - line * P.sx;
             const int kq = small_div(line, rpj), jj = J0 + P.hj + (line - kq * P.pj), kk = K0 + P.hk + kq;
             S v[8], w = from_t<S>((T)0);
 #pragma unroll
@@ -262,14 +271,14 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(const SweepArgs P, cons
                 const int bx = ext_x(c), by = ext_y(c);
                 v[c] = from_t<S>((T)0);
                 if (ii < bx && (unsigned)jj < (unsigned)by && (unsigned)kk < (unsigned)ext_z(c)) {
-                    v[c] = zin[(i64)(P.off[c] + ii + bx * (jj + by * kk)) * K + rhs];
-                    if (c == 4 && zc) w = zc[(i64)coarse_index(P, ii, jj, kk) * K + rhs];
+                    v[c] = zin[(i64)(P.off[c] + ii + bx * (jj + by * kk)) * K + j];
+                    if (c == 4 && zc) w = zc[(i64)coarse_index(P, ii, jj, kk) * K + j];
                 }
             }
             sched_fence();
             if (zc) v[4] = from_t<S>(to_t<T>(v[4]) + to_t<T>(w));
 #pragma unroll
-            for (int c = 0; c < 8; ++c) zs[(1 + c * block + t) * K + rhs] = v[c];
+            for (int c = 0; c < 8; ++c) zs[(1 + c * block + t) * K + j] = v[c];
         }
     } else {
         const int words = ((1 + 8 * block) * K * (int)sizeof(S) + 15) / 16;
@@ -291,12 +300,20 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(const SweepArgs P, cons
         if (npos <= last) fetch(npos, nchunk, F);
         sched_fence();
         if (E.act) {
-            const T acc = row_sum(pos, E);
+            T acc[R];
+            Pack<S, R> out;
+            row_sum(pos, E, acc);
             if (pos < 8) {
-                zs[E.cell] = from_t<S>((to_t<T>(E.r) - acc) / to_t<T>(E.d));
+#pragma unroll
+                for (int i = 0; i < R; ++i) out.v[i] = from_t<S>((to_t<T>(E.r.v[i]) - acc[i]) / to_t<T>(E.d));
+                stp<S, R>(zs + E.cell, out);
             } else {  // the colour-4 block is the coarse level in its natural order
-                const T v = P.tail == 1 ? -acc : to_t<T>(E.r) - (to_t<T>(E.d) * to_t<T>(zs[E.cell]) + acc);
-                rc[(i64)coarse_index(P, E.ii, E.jj, E.kk) * K + rhs] = from_t<S>(v);
+                const Pack<S, R> own = ldp<S, R>(zs + E.cell);
+#pragma unroll
+                for (int i = 0; i < R; ++i)
+                    out.v[i] = from_t<S>(P.tail == 1 ? -acc[i]
+                                                     : to_t<T>(E.r.v[i]) - (to_t<T>(E.d) * to_t<T>(own.v[i]) + acc[i]));
+                stp<S, R>(rc + ((i64)coarse_index(P, E.ii, E.jj, E.kk) * K + rhs), out);
             }
         }
         if (npos > last) return true;
@@ -314,14 +331,14 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(const SweepArgs P, cons
     // the tile's own rows
     const float rn = recip(P.n);
     for (int e = tid; e < bxe * P.n * P.m * K; e += nt) {
-        const int t = e / K, line = small_div(t, rbx), ii = t - line * bxe;
+        const int t = e / K, j = e % K, line = small_div(t, rbx), ii = t - line * bxe;
         const int kq = small_div(line, rn), jq = line - kq * P.n, jj = J0 + jq, kk = K0 + kq;
         const int cell = 1 + ii + P.sx * ((jq - P.hj) + P.pj * (kq - P.hk));
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             const int bx = ext_x(c), by = ext_y(c);
             if (ii < bx && jj < by && kk < ext_z(c))
-                zout[(i64)(P.off[c] + ii + bx * (jj + by * kk)) * K + rhs] = zs[(cell + c * block) * K + rhs];
+                zout[(i64)(P.off[c] + ii + bx * (jj + by * kk)) * K + j] = zs[(cell + c * block) * K + j];
         }
     }
 }
@@ -408,15 +425,15 @@ int sweep_tiles(const Geom &g, int n, int m)
 
 // Lanes at work at position q, of the arguments P for tiles of one cell, when
 // the tiles have n x m cells (every box grows with its tile).
-i64 sweep_lanes(const SweepArgs &P, int q, int n, int m, int K)
+i64 sweep_lanes(const SweepArgs &P, int q, int n, int m, int L)
 {
-    return (i64)(P.nx1 >> 1) * ((P.pos[q] >> 4 & 31) - 1 + n) * ((P.pos[q] >> 13 & 31) - 1 + m) * K;
+    return (i64)(P.nx1 >> 1) * ((P.pos[q] >> 4 & 31) - 1 + n) * ((P.pos[q] >> 13 & 31) - 1 + m) * L;
 }
 
 // The tile whose workgroups, taken one per CU, have the fewest row chunks to
 // work through one after the other; of equal ones the smallest.  Returns the
 // LDS bytes of a workgroup.
-size_t choose_tile(const Geom &g, const SweepArgs &P, int K, size_t vb, int &n, int &m)
+size_t choose_tile(const Geom &g, const SweepArgs &P, int K, int L, size_t vb, int &n, int &m)
 {
     i64 best = -1;
     size_t lds = 0;
@@ -426,7 +443,7 @@ size_t choose_tile(const Geom &g, const SweepArgs &P, int K, size_t vb, int &n, 
             const size_t b = ((size_t)cells * K * vb + 15) / 16 * 16;
             if (b > kSweepLds) break;
             i64 items = 0;
-            for (int q = P.first; q < 8; ++q) items += (sweep_lanes(P, q, nn, mm, K) + kSweepThreads - 1) / kSweepThreads;
+            for (int q = P.first; q < 8; ++q) items += (sweep_lanes(P, q, nn, mm, L) + kSweepThreads - 1) / kSweepThreads;
             const i64 cost = (sweep_tiles(g, nn, mm) + kCus - 1) / kCus * items;
             if (best < 0 || cost < best) { best = cost; n = nn; m = mm; lds = b; }
         }
@@ -437,10 +454,10 @@ template <typename V, typename S, int K>
 void sweep_launch(const V *v, const V *d, const SweepArgs &P, int tiles, int threads, size_t lds, const void *r,
                   const void *zin, const void *zc, void *zout, void *rc, hipStream_t s)
 {
-    if (lds > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sweep<V, S, K>),
+    if (lds > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sweep<V, S, K, kSweepR<K>>),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         throw std::runtime_error("launch_sweep: the device refuses the workgroup's LDS");
-    hipLaunchKernelGGL((k_sweep<V, S, K>), dim3(tiles), dim3(threads), lds, s, P, v, d, (const S *)r, (const S *)zin,
+    hipLaunchKernelGGL((k_sweep<V, S, K, kSweepR<K>>), dim3(tiles), dim3(threads), lds, s, P, v, d, (const S *)r, (const S *)zin,
                        (const S *)zc, (S *)zout, (S *)rc);
 }
 
@@ -463,13 +480,14 @@ void launch_sweep(const Matrix &A, Prec p, int K, bool forward, bool skip_first,
     const Geom &g = A.g;
     SweepArgs one{}, P{};
     sweep_args(one, g, gc, 1, 1, forward, zero, skip_first, tail);
+    const int L = K / (K == 8 ? kSweepR<8> : K == 4 ? kSweepR<4> : K == 2 ? kSweepR<2> : 1);
     int n = 1, m = 1;
-    const size_t lds = choose_tile(g, one, K, vec_bytes(p), n, m);
+    const size_t lds = choose_tile(g, one, K, L, vec_bytes(p), n, m);
     sweep_args(P, g, gc, n, m, forward, zero, skip_first, tail);
     P.remap = tile_remap(A);
     P.bytes = (unsigned)(ell_entries(g.N, A.clog2) * (i64)(p == P64 ? 8 : p == P32 ? 4 : 2));
     i64 lanes = 64;
-    for (int q = P.first; q < 8; ++q) lanes = std::max(lanes, sweep_lanes(one, q, n, m, K));
+    for (int q = P.first; q < 8; ++q) lanes = std::max(lanes, sweep_lanes(one, q, n, m, L));
     const int threads = (int)std::min<i64>(kSweepThreads, (lanes + 63) / 64 * 64);
     const int tiles = sweep_tiles(g, n, m);
     auto go = [&](auto *v, auto *d, auto sv) {
