@@ -309,12 +309,9 @@ void *gathered_vector(hpgmx_ctx *c, i64 N, Prec p)
     return v;
 }
 
-// The staging buffers serve every level: re-zero entry N of the level used.
-void zero_entry(hpgmx_ctx *c, void *v, i64 N, Prec p)
-{
-    hip_check(hipMemsetAsync((char *)v + (size_t)N * vec_bytes(p), 0, vec_bytes(p), c->stream),
-              "hipMemsetAsync");
-}
+// Entry N of a staging buffer: these serve every level, so the permutation
+// that fills one clears the entry of the level used.
+void *entry(void *v, i64 N, Prec p) { return (char *)v + (size_t)N * vec_bytes(p); }
 
 // Levels whose half-sweeps run as one launch each (launch_sweep): those
 // where a launch per colour is bound by latency, up to kSweepBytes bytes of
@@ -939,13 +936,6 @@ void *gathered_batch(hpgmx_ctx *c, i64 N, int K, Prec p)
     char *v = (char *)c->dalloc((size_t)(N + 1) * K * vb);
     hip_check(hipMemsetAsync(v + (size_t)N * K * vb, 0, K * vb, c->stream), "hipMemsetAsync");
     return v;
-}
-
-// The staging buffers serve every level: re-zero row N of the level used.
-void zero_batch_row(hpgmx_ctx *c, void *v, i64 N, int K, Prec p)
-{
-    const size_t vb = vec_bytes(p);
-    hip_check(hipMemsetAsync((char *)v + (size_t)N * K * vb, 0, K * vb, c->stream), "hipMemsetAsync");
 }
 
 Batch &ensure_batch(hpgmx_ctx *c, int K)
@@ -1716,8 +1706,8 @@ hpgmx_status hpgmx_spmv(hpgmx_handle h, int level, int dtype, const void *x, voi
         const Prec pv = vprec(p), py = basis_prec(p);  // y is a Krylov vector
         ensure_tmp(h, py);
         void *ty = h->tmp[vt_of(py)][1];
-        zero_entry(h, h->tmp[vt][0], A.g.N, pv);
-        launch_nat2int(A.g, pv, x, pv, h->tmp[vt][0], h->stream);
+        launch_nat2int(A.g, pv, x, pv, h->tmp[vt][0], h->stream,
+                       entry(h->tmp[vt][0], A.g.N, pv));
         launch_spmv(A, p, h->tmp[vt][0], ty, h->stream);
         launch_int2nat(A.g, py, ty, py, y, h->stream);
         return HPGMX_OK;
@@ -1739,8 +1729,8 @@ hpgmx_status hpgmx_smooth(hpgmx_handle h, int level, int dtype, int sweep, const
         const int vt = vt_of(p);
         const Matrix &A = h->lv[level].A;
         const Prec pv = vprec(p);
-        zero_entry(h, h->tmp[vt][1], A.g.N, pv);
-        launch_nat2int(A.g, pv, r, pv, h->tmp[vt][0], h->stream);
+        launch_nat2int(A.g, pv, r, pv, h->tmp[vt][0], h->stream,
+                       entry(h->tmp[vt][1], A.g.N, pv));
         if (!zero_guess) launch_nat2int(A.g, pv, z, pv, h->tmp[vt][1], h->stream);
         void *out = h->tmp[vt][1];
         if (tiled(h, level, p, 1)) {
@@ -1769,8 +1759,8 @@ hpgmx_status hpgmx_vcycle(hpgmx_handle h, int dtype, const void *r, void *z)
         const int vt = vt_of(p);
         const Matrix &A = h->lv[0].A;
         const Prec pv = vprec(p);
-        zero_entry(h, h->tmp[vt][1], A.g.N, pv);
-        launch_nat2int(A.g, pv, r, pv, h->tmp[vt][0], h->stream);
+        launch_nat2int(A.g, pv, r, pv, h->tmp[vt][0], h->stream,
+                       entry(h->tmp[vt][1], A.g.N, pv));
         vcycle(h, 0, p, h->tmp[vt][0], h->tmp[vt][1], {}, h->tmp[vt][2]);
         launch_int2nat(A.g, pv, h->tmp[vt][1], pv, z, h->stream);
         return HPGMX_OK;
@@ -1793,8 +1783,8 @@ hpgmx_status hpgmx_restrict_residual(hpgmx_handle h, int level, int dtype, const
         const Matrix &A = h->lv[level].A;
         const Geom &gc = h->lv[level + 1].A.g;
         const Prec pv = vprec(p);
-        zero_entry(h, h->tmp[vt][1], A.g.N, pv);
-        launch_nat2int(A.g, pv, r, pv, h->tmp[vt][0], h->stream);
+        launch_nat2int(A.g, pv, r, pv, h->tmp[vt][0], h->stream,
+                       entry(h->tmp[vt][1], A.g.N, pv));
         launch_nat2int(A.g, pv, z, pv, h->tmp[vt][1], h->stream);
         launch_restrict(A, gc, p, h->tmp[vt][0], h->tmp[vt][1], h->tmp[vt][2], h->stream);
         launch_int2nat(gc, pv, h->tmp[vt][2], pv, r_coarse, h->stream);
@@ -1820,8 +1810,8 @@ hpgmx_status hpgmx_presmooth_restrict(hpgmx_handle h, int level, int dtype, int 
         const Matrix &A = h->lv[level].A;
         const Geom &gc = h->lv[level + 1].A.g;
         const Prec pv = vprec(p);
-        zero_entry(h, h->tmp[vt][1], A.g.N, pv);
-        launch_nat2int(A.g, pv, r, pv, h->tmp[vt][0], h->stream);
+        launch_nat2int(A.g, pv, r, pv, h->tmp[vt][0], h->stream,
+                       entry(h->tmp[vt][1], A.g.N, pv));
         presmooth_restrict(h, level, p, sweep, nsweeps, h->tmp[vt][0], h->tmp[vt][1], h->tmp[vt][2]);
         launch_int2nat(A.g, pv, h->tmp[vt][1], pv, z, h->stream);
         launch_int2nat(gc, pv, h->tmp[vt][2], pv, r_coarse, h->stream);
@@ -1892,8 +1882,8 @@ hpgmx_status hpgmx_rhs_from_x(hpgmx_handle h, const double *x, double *b)
         check_ptr(b, "b");
         ensure_tmp(h, P64);
         const Matrix &A = h->lv[0].A;
-        zero_entry(h, h->tmp[0][0], A.g.N, P64);
-        launch_nat2int(A.g, P64, x, P64, h->tmp[0][0], h->stream);
+        launch_nat2int(A.g, P64, x, P64, h->tmp[0][0], h->stream,
+                       entry(h->tmp[0][0], A.g.N, P64));
         launch_spmv(A, P64, h->tmp[0][0], h->tmp[0][1], h->stream);
         launch_int2nat(A.g, P64, h->tmp[0][1], P64, b, h->stream);
         return HPGMX_OK;
@@ -1910,8 +1900,8 @@ hpgmx_status hpgmx_stencil_grad(hpgmx_handle h, const double *lam, const double 
         ensure_common(h);
         ensure_tmp(h, P64);
         const Matrix &A = h->lv[0].A;
-        zero_entry(h, h->tmp[0][1], A.g.N, P64);
-        launch_nat2int(A.g, P64, lam, P64, h->tmp[0][0], h->stream);
+        launch_nat2int(A.g, P64, lam, P64, h->tmp[0][0], h->stream,
+                       entry(h->tmp[0][1], A.g.N, P64));
         launch_nat2int(A.g, P64, x, P64, h->tmp[0][1], h->stream);
         launch_stencil_correlation(A, (const double *)h->tmp[0][0], (const double *)h->tmp[0][1],
                                    h->partials, h->ctrl, h->stream);
@@ -2021,8 +2011,8 @@ hpgmx_status hpgmx_spmv_batched(hpgmx_handle h, int level, int dtype, int nrhs, 
         ensure_batch_prec(h, B, p, 0);
         ensure_batch_tmp(h, B, vt);
         const Matrix &A = h->lv[level].A;
-        zero_batch_row(h, B.tmp[vt][0], A.g.N, K, p);
-        launch_bnat2int(A.g, p, p, K, nrhs, X, B.tmp[vt][0], h->stream);
+        launch_bnat2int(A.g, p, p, K, nrhs, X, B.tmp[vt][0], h->stream,
+                        entry(B.tmp[vt][0], A.g.N * K, p));
         launch_bspmv(A, p, K, tile_r(h, B, p, HPGMX_BK_SPMV, level), B.tmp[vt][0], B.tmp[vt][1], h->stream);
         launch_bint2nat(A.g, p, p, K, nrhs, B.tmp[vt][1], Y, h->stream);
         return HPGMX_OK;
@@ -2046,8 +2036,8 @@ hpgmx_status hpgmx_smooth_batched(hpgmx_handle h, int level, int dtype, int swee
         ensure_batch_prec(h, B, p, 0);
         ensure_batch_tmp(h, B, vt);
         const Matrix &A = h->lv[level].A;
-        zero_batch_row(h, B.tmp[vt][1], A.g.N, K, p);
-        launch_bnat2int(A.g, p, p, K, nrhs, R, B.tmp[vt][0], h->stream);
+        launch_bnat2int(A.g, p, p, K, nrhs, R, B.tmp[vt][0], h->stream,
+                        entry(B.tmp[vt][1], A.g.N * K, p));
         if (!zero_guess) launch_bnat2int(A.g, p, p, K, nrhs, Z, B.tmp[vt][1], h->stream);
         void *out = B.tmp[vt][1];
         if (btiled(h, B, level, p)) {
@@ -2083,8 +2073,8 @@ hpgmx_status hpgmx_presmooth_restrict_batched(hpgmx_handle h, int level, int dty
         ensure_batch_tmp(h, B, vt);
         const Matrix &A = h->lv[level].A;
         const Geom &gc = h->lv[level + 1].A.g;
-        zero_batch_row(h, B.tmp[vt][1], A.g.N, K, p);
-        launch_bnat2int(A.g, p, p, K, nrhs, R, B.tmp[vt][0], h->stream);
+        launch_bnat2int(A.g, p, p, K, nrhs, R, B.tmp[vt][0], h->stream,
+                        entry(B.tmp[vt][1], A.g.N * K, p));
         bpresmooth_restrict(h, B, level, p, sweep, nsweeps, B.tmp[vt][0], B.tmp[vt][1], B.tmp[vt][2]);
         launch_bint2nat(A.g, p, p, K, nrhs, B.tmp[vt][1], Z, h->stream);
         launch_bint2nat(gc, p, p, K, nrhs, B.tmp[vt][2], R_coarse, h->stream);
@@ -2106,8 +2096,8 @@ hpgmx_status hpgmx_vcycle_batched(hpgmx_handle h, int dtype, int nrhs, const voi
         ensure_batch_prec(h, B, p, 0);
         ensure_batch_tmp(h, B, vt);
         const Matrix &A = h->lv[0].A;
-        zero_batch_row(h, B.tmp[vt][1], A.g.N, K, p);
-        launch_bnat2int(A.g, p, p, K, nrhs, R, B.tmp[vt][0], h->stream);
+        launch_bnat2int(A.g, p, p, K, nrhs, R, B.tmp[vt][0], h->stream,
+                        entry(B.tmp[vt][1], A.g.N * K, p));
         bvcycle(h, B, 0, p, B.tmp[vt][0], B.tmp[vt][1], {}, B.tmp[vt][2]);
         launch_bint2nat(A.g, p, p, K, nrhs, B.tmp[vt][1], Z, h->stream);
         return HPGMX_OK;

@@ -287,12 +287,14 @@ __global__ __launch_bounds__(kBlock) void k_bresid64(i64 N, int clog2, int remap
 // ---- [nrhs][N] natural order <-> [N][K] colour-blocked --------------------------------------
 template <typename Ti, typename To, int K>
 __global__ __launch_bounds__(kBlock) void k_bnat2int(Geom g, int nrhs, const Ti *__restrict__ nat,
-                                                     To *__restrict__ in)
+                                                     To *__restrict__ in, To *zero)
 {
-    const i64 I = gtid();
-    if (I >= g.N) return;
-    const int i = (int)(I % g.nx), j = (int)((I / g.nx) % g.ny), k = (int)(I / ((i64)g.nx * g.ny));
-    const i64 q = to_internal(g, i, j, k) * K;
+    const unsigned I = blockIdx.x * kBlock + threadIdx.x;  // N < 2^31
+    if (I < K && zero) zero[I] = (To)0;
+    if (I >= (unsigned)g.N) return;
+    const unsigned line = I / (unsigned)g.nx, k = line / (unsigned)g.ny;
+    const int i = (int)(I - line * g.nx), j = (int)(line - k * g.ny);
+    const i64 q = to_internal(g, i, j, (int)k) * K;
 #pragma unroll
     for (int c = 0; c < K; ++c) in[q + c] = c < nrhs ? (To)nat[(i64)c * g.N + I] : (To)0;
 }
@@ -301,10 +303,11 @@ template <typename Ti, typename To, int K>
 __global__ __launch_bounds__(kBlock) void k_bint2nat(Geom g, int nrhs, const Ti *__restrict__ in,
                                                      To *__restrict__ nat)
 {
-    const i64 I = gtid();
-    if (I >= g.N) return;
-    const int i = (int)(I % g.nx), j = (int)((I / g.nx) % g.ny), k = (int)(I / ((i64)g.nx * g.ny));
-    const i64 q = to_internal(g, i, j, k) * K;
+    const unsigned I = blockIdx.x * kBlock + threadIdx.x;  // N < 2^31
+    if (I >= (unsigned)g.N) return;
+    const unsigned line = I / (unsigned)g.nx, k = line / (unsigned)g.ny;
+    const int i = (int)(I - line * g.nx), j = (int)(line - k * g.ny);
+    const i64 q = to_internal(g, i, j, (int)k) * K;
 #pragma unroll
     for (int c = 0; c < K; ++c)
         if (c < nrhs) nat[(i64)c * g.N + I] = (To)in[q + c];
@@ -589,16 +592,16 @@ void launch_bresid64(const Matrix &A, int K, int R, const double *x, const doubl
 }
 
 void launch_bnat2int(const Geom &g, Prec src, Prec dst, int K, int nrhs, const void *nat, void *in,
-                     hipStream_t s)
+                     hipStream_t s, void *zero)
 {
     const dim3 gr(grid_for(g.N)), bl(kBlock);
     with_k(K, [&](auto kc) {
         constexpr int KK = decltype(kc)::value;
         const bool s64 = src == P64, d64 = dst == P64;
-        if (s64 && d64) hipLaunchKernelGGL((k_bnat2int<double, double, KK>), gr, bl, 0, s, g, nrhs, (const double *)nat, (double *)in);
-        else if (s64) hipLaunchKernelGGL((k_bnat2int<double, float, KK>), gr, bl, 0, s, g, nrhs, (const double *)nat, (float *)in);
-        else if (d64) hipLaunchKernelGGL((k_bnat2int<float, double, KK>), gr, bl, 0, s, g, nrhs, (const float *)nat, (double *)in);
-        else hipLaunchKernelGGL((k_bnat2int<float, float, KK>), gr, bl, 0, s, g, nrhs, (const float *)nat, (float *)in);
+        if (s64 && d64) hipLaunchKernelGGL((k_bnat2int<double, double, KK>), gr, bl, 0, s, g, nrhs, (const double *)nat, (double *)in, (double *)zero);
+        else if (s64) hipLaunchKernelGGL((k_bnat2int<double, float, KK>), gr, bl, 0, s, g, nrhs, (const double *)nat, (float *)in, (float *)zero);
+        else if (d64) hipLaunchKernelGGL((k_bnat2int<float, double, KK>), gr, bl, 0, s, g, nrhs, (const float *)nat, (double *)in, (double *)zero);
+        else hipLaunchKernelGGL((k_bnat2int<float, float, KK>), gr, bl, 0, s, g, nrhs, (const float *)nat, (float *)in, (float *)zero);
     });
     HPGMX_LAUNCH_CHECK();
 }

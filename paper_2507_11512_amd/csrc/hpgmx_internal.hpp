@@ -266,7 +266,10 @@ hipError_t noalloc_setup(int device);
 size_t noalloc_scratch_bytes();
 void launch_stencil_correlation_noalloc(int device, const Geom &g, const double *lam, const double *x,
                                         double *out27, hipStream_t s);
-void launch_nat2int(const Geom &g, Prec src, const void *nat, Prec dst, void *in, hipStream_t s);
+// `zero`: an element of type dst to clear in the same launch (the zero entry
+// of a vector the kernels gather from), or null.
+void launch_nat2int(const Geom &g, Prec src, const void *nat, Prec dst, void *in, hipStream_t s,
+                    void *zero = nullptr);
 void launch_int2nat(const Geom &g, Prec src, const void *in, Prec dst, void *nat, hipStream_t s);
 // y = A x; with ctrl, y = (A x) * ctrl->colscale[k] (the SpMV of inner step
 // k, fed with the unnormalised basis column k), or for the 16-bit hierarchy
@@ -420,8 +423,9 @@ void launch_bresid64(const Matrix &A, int K, int R, const double *x, const doubl
                      double *partials, Ctrl *ctrl, int m, hipStream_t s);
 // [nrhs][N] natural order <-> [N][K] colour-blocked interleaved (right-hand
 // sides nrhs..K-1 are zero-filled on the way in and dropped on the way out).
+// `zero`: a row of K elements of type dst to clear in the same launch, or null.
 void launch_bnat2int(const Geom &g, Prec src, Prec dst, int K, int nrhs, const void *nat, void *in,
-                     hipStream_t s);
+                     hipStream_t s, void *zero = nullptr);
 void launch_bint2nat(const Geom &g, Prec src, Prec dst, int K, int nrhs, const void *in, void *nat,
                      hipStream_t s);
 
