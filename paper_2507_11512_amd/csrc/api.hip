@@ -640,20 +640,26 @@ struct Scal {  // mirrors the scalar block of Ctrl
     int breakdown, nonfinite;
 };
 
-Scal read_scal(hpgmx_ctx *c)
+// The finish kernels write the scalar blocks of K right-hand sides to pinned
+// memory, kScalWords words each, slot 0 or 1 of `host`.
+double *scal_slot(double *host, int K, int slot) { return host + (size_t)slot * K * kScalWords; }
+
+void copy_scal(const double *from, int K, Scal *out)
 {
-    hip_check(hipMemcpyAsync(c->host_scal, &c->ctrl->rho, sizeof(Scal), hipMemcpyDeviceToHost,
-                             c->stream), "hipMemcpyAsync");
+    for (int j = 0; j < K; ++j) std::memcpy(out + j, from + (size_t)j * kScalWords, sizeof(Scal));
+}
+
+// The scalars of the last finish kernel, which went to slot 0.
+void read_scal(hpgmx_ctx *c, int K, const double *host, Scal *out)
+{
     hip_check(hipStreamSynchronize(c->stream), "hipStreamSynchronize");
-    Scal s;
-    std::memcpy(&s, c->host_scal, sizeof(Scal));
-    return s;
+    copy_scal(host, K, out);
 }
 
 // Inner steps are pipelined one deep: the host enqueues step k + 1 before it
 // waits for the scalars of step k, so the GPU does not idle for the host's
-// round trip.  The copy of step k's scalars goes to slot k & 1 of the
-// pinned buffer and the host waits on that slot's event only.  A step
+// round trip.  Step k's scalars go to slot k & 1 of the pinned buffer and
+// the host waits on that slot's event only.  A step
 // enqueued past the end of a cycle (convergence, breakdown) is discarded: it
 // writes only Hessenberg column k + 1, t from index k + 1 on and basis
 // column k + 2, which the back-solve and the basis combination of a cycle
@@ -665,23 +671,12 @@ void ensure_scal_events(hpgmx_ctx *c)
         if (!e) hip_check(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
 }
 
-void enqueue_scal(hpgmx_ctx *c, const Ctrl *ctrl, int K, double *host, int slot)
-{
-    char *dst = (char *)host + (size_t)slot * K * 64;
-    if (K == 1)
-        hip_check(hipMemcpyAsync(dst, &ctrl->rho, sizeof(Scal), hipMemcpyDeviceToHost, c->stream),
-                  "hipMemcpyAsync");
-    else
-        hip_check(hipMemcpy2DAsync(dst, sizeof(Scal), &ctrl[0].rho, sizeof(Ctrl), sizeof(Scal), K,
-                                   hipMemcpyDeviceToHost, c->stream),
-                  "hipMemcpy2DAsync");
-    hip_check(hipEventRecord(c->ev_scal[slot], c->stream), "hipEventRecord");
-}
+void mark_scal(hpgmx_ctx *c, int slot) { hip_check(hipEventRecord(c->ev_scal[slot], c->stream), "hipEventRecord"); }
 
-void wait_scal(hpgmx_ctx *c, int K, const double *host, int slot, Scal *out)
+void wait_scal(hpgmx_ctx *c, int K, double *host, int slot, Scal *out)
 {
     hip_check(hipEventSynchronize(c->ev_scal[slot]), "hipEventSynchronize");
-    std::memcpy(out, (const char *)host + (size_t)slot * K * 64, K * sizeof(Scal));
+    copy_scal(scal_slot(host, K, slot), K, out);
 }
 
 // Graph replay needs a capturable stream and no memset nodes (a level with
@@ -783,8 +778,9 @@ hpgmx_status solve(hpgmx_ctx *c, const double *b, double *x, const hpgmx_solve_d
         ProfScope ps(c, HPGMX_K_PERMUTE, 0);
         launch_nat2int(g0, P64, x, P64, c->x_int, c->stream);
     }
-    launch_norm64(N, 1, c->b_int, c->partials, c->ctrl, kFinishRho0, 0, c->stream);
-    Scal sc = read_scal(c);
+    launch_norm64(N, 1, c->b_int, c->partials, c->ctrl, kFinishRho0, 0, c->stream, c->host_scal);
+    Scal sc;
+    read_scal(c, 1, c->host_scal, &sc);
     const double rho0 = sc.rho0;
     S.rho0 = rho0;
     hpgmx_status status = HPGMX_OK;
@@ -800,9 +796,9 @@ hpgmx_status solve(hpgmx_ctx *c, const double *b, double *x, const hpgmx_solve_d
         for (;;) {
             {
                 PassScope ps(c, HPGMX_K_RESID64, 0);
-                launch_resid64(A0, c->x_int, c->b_int, c->r64, c->partials, c->ctrl, m, c->stream);
+                launch_resid64(A0, c->x_int, c->b_int, c->r64, c->partials, c->ctrl, m, c->stream, c->host_scal);
             }
-            sc = read_scal(c);
+            read_scal(c, 1, c->host_scal, &sc);
             double rho = sc.rho;
             S.final_rel_res = rho / rho0;
             if (sc.nonfinite) { status = HPGMX_ENONFINITE; c->err = "outer residual is not finite"; break; }
@@ -815,7 +811,7 @@ hpgmx_status solve(hpgmx_ctx *c, const double *b, double *x, const hpgmx_solve_d
             int kk = 0;
             ensure_scal_events(c);
             // one inner step: z = M^{-1} q_k, w = A z, CGS2, Givens, q_{k+1},
-            // then the copy of its scalars (see enqueue_scal)
+            // its scalars to the host (see scal_slot)
             auto run_step = [&](int k) {
                 auto step = [&]() {
                     // w = A z: with kSpmvLast the rows of colour fc come from
@@ -857,12 +853,13 @@ hpgmx_status solve(hpgmx_ctx *c, const double *b, double *x, const hpgmx_solve_d
                     }
                     {
                         PassScope ps(c, HPGMX_K_CGS_NORM, 0);
-                        launch_cgs_norm(N, 1, bp, K.Q, ldq, k + 1, col(k + 1), c->partials, c->ctrl, k, m, c->stream);
+                        launch_cgs_norm(N, 1, bp, K.Q, ldq, k + 1, col(k + 1), c->partials, c->ctrl, k, m, c->stream,
+                                        scal_slot(c->host_scal, 1, k & 1));
                     }
                 };
                 if (use_graph) replay_step(c, std::make_tuple((int)p, k, m, 1), step);
                 else step();
-                enqueue_scal(c, c->ctrl, 1, c->host_scal, k & 1);
+                mark_scal(c, k & 1);
             };
             if (!(rho / rho0 < d->tol)) {
                 run_step(0);
@@ -950,7 +947,7 @@ Batch &ensure_batch(hpgmx_ctx *c, int K)
     hip_check(hipMemsetAsync(B.ctrl, 0, K * sizeof(Ctrl), c->stream), "hipMemsetAsync");
     B.partials = (double *)c->dalloc((size_t)kMaxRedBlocks * kMaxBasis * K * 8);
     if (!B.host_scal)
-        hip_check(hipHostMalloc((void **)&B.host_scal, (size_t)2 * K * 64, hipHostMallocDefault), "hipHostMalloc");
+        hip_check(hipHostMalloc((void **)&B.host_scal, (size_t)2 * K * kScalWords * 8, hipHostMallocDefault), "hipHostMalloc");
     B.K = K;
     return B;
 }
@@ -1157,7 +1154,7 @@ void autotune(hpgmx_ctx *c, Batch &B, Prec p)
             if (l == 0)
                 t[HPGMX_BK_RESID64] = time_it([&] {
                     launch_bresid64(A, K, R, (const double *)B.tmp[0][0], (const double *)B.tmp[0][1],
-                                    (double *)B.tmp[0][2], B.partials, B.ctrl, 1, c->stream);
+                                    (double *)B.tmp[0][2], B.partials, B.ctrl, 1, c->stream, nullptr);
                 });
             for (int k = 0; k < HPGMX_BK_COUNT; ++k) {
                 if (t[k] < 0.0) continue;
@@ -1176,15 +1173,6 @@ void autotune(hpgmx_ctx *c, Batch &B, Prec p)
     T.set = true;
     B.tune[p] = T;
     c->drop_graphs();  // captured steps hold the old tiles
-}
-
-void read_scal_batch(hpgmx_ctx *c, Batch &B, Scal *out)
-{
-    hip_check(hipMemcpy2DAsync(B.host_scal, sizeof(Scal), &B.ctrl[0].rho, sizeof(Ctrl), sizeof(Scal), B.K,
-                               hipMemcpyDeviceToHost, c->stream),
-              "hipMemcpy2DAsync");
-    hip_check(hipStreamSynchronize(c->stream), "hipStreamSynchronize");
-    std::memcpy(out, B.host_scal, B.K * sizeof(Scal));
 }
 
 hpgmx_status bsolve(hpgmx_ctx *c, int nrhs, const double *Bn, double *Xn, const hpgmx_solve_desc *d,
@@ -1226,9 +1214,9 @@ hpgmx_status bsolve(hpgmx_ctx *c, int nrhs, const double *Bn, double *Xn, const 
         ProfScope ps(c, HPGMX_K_PERMUTE, 0);
         launch_bnat2int(g0, P64, P64, K, nrhs, Xn, B.x, c->stream);
     }
-    launch_norm64(M, K, B.b, B.partials, B.ctrl, kFinishRho0, 0, c->stream);
+    launch_norm64(M, K, B.b, B.partials, B.ctrl, kFinishRho0, 0, c->stream, B.host_scal);
     Scal sc[kMaxBatch];
-    read_scal_batch(c, B, sc);
+    read_scal(c, K, B.host_scal, sc);
     double rho0[kMaxBatch], rho[kMaxBatch];
     bool done[kMaxBatch];
     int its[kMaxBatch] = {};
@@ -1248,9 +1236,9 @@ hpgmx_status bsolve(hpgmx_ctx *c, int nrhs, const double *Bn, double *Xn, const 
             {
                 PassScope ps(c, HPGMX_K_RESID64, 0);
                 launch_bresid64(A0, K, tile_r(c, B, p, HPGMX_BK_RESID64, 0), B.x, B.b, B.r64, B.partials, B.ctrl,
-                                m, c->stream);
+                                m, c->stream, B.host_scal);
             }
-            read_scal_batch(c, B, sc);
+            read_scal(c, K, B.host_scal, sc);
             bool bad = false, any = false;
             for (int j = 0; j < K; ++j) {
                 rho[j] = sc[j].rho;
@@ -1273,8 +1261,8 @@ hpgmx_status bsolve(hpgmx_ctx *c, int nrhs, const double *Bn, double *Xn, const 
             bool nonfin = false;
             ensure_scal_events(c);
             // one inner step for every right-hand side: z = M^{-1} q_k, w = A z,
-            // CGS2, Givens, q_{k+1}, then the copy of the scalars (pipelined one
-            // deep as in solve(); see enqueue_scal)
+            // CGS2, Givens, q_{k+1}, the scalars to the host (pipelined one deep
+            // as in solve(); see scal_slot)
             auto run_step = [&](int k) {
                 auto step = [&]() {
                     // w = A z shared with the V-cycle's last sweep as in solve()
@@ -1306,12 +1294,13 @@ hpgmx_status bsolve(hpgmx_ctx *c, int nrhs, const double *Bn, double *Xn, const 
                     }
                     {
                         PassScope ps(c, HPGMX_K_CGS_NORM, 0);
-                        launch_cgs_norm(M, K, p, Kr.Q, ldq, k + 1, col(k + 1), B.partials, B.ctrl, k, m, c->stream);
+                        launch_cgs_norm(M, K, p, Kr.Q, ldq, k + 1, col(k + 1), B.partials, B.ctrl, k, m, c->stream,
+                                        scal_slot(B.host_scal, K, k & 1));
                     }
                 };
                 if (use_graph) replay_step(c, std::make_tuple((int)p, k, m, K), step);
                 else step();
-                enqueue_scal(c, B.ctrl, K, B.host_scal, k & 1);
+                mark_scal(c, k & 1);
             };
             // right-hand sides still taking steps in this cycle (the test at
             // the top of Alg. 3's inner loop)

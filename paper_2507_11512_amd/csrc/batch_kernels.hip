@@ -580,7 +580,7 @@ void launch_bprolong(const Geom &gf, const Geom &gc, Prec p, int K, const void *
 }
 
 void launch_bresid64(const Matrix &A, int K, int R, const double *x, const double *b, double *r,
-                     double *partials, Ctrl *ctrl, int m, hipStream_t s)
+                     double *partials, Ctrl *ctrl, int m, hipStream_t s, double *host)
 {
     with_kr(K, R, [&](auto kc, auto rc) {
         constexpr int KK = decltype(kc)::value, RR = decltype(rc)::value;
@@ -588,7 +588,7 @@ void launch_bresid64(const Matrix &A, int K, int R, const double *x, const doubl
                            A.clog2, tile_remap(A), A.v64, (const int *)A.col, A.d64, x, b, r);
     });
     HPGMX_LAUNCH_CHECK();
-    launch_norm64(A.g.N * K, K, r, partials, ctrl, kFinishResid, m, s);
+    launch_norm64(A.g.N * K, K, r, partials, ctrl, kFinishResid, m, s, host);
 }
 
 void launch_bnat2int(const Geom &g, Prec src, Prec dst, int K, int nrhs, const void *nat, void *in,

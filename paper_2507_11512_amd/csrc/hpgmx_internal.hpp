@@ -341,9 +341,13 @@ void launch_prolong(const Geom &gf, const Geom &gc, Prec p, const void *zc, void
 // elements.
 int red_blocks(i64 N);
 // The finish kernel: one workgroup per right-hand side adds partial columns
-// i * K + j (i < kb) over nb workgroups and applies `mode` to ctrl[j].
+// i * K + j (i < kb) over nb workgroups and applies `mode` to ctrl[j] (for h1
+// and h2 one workgroup per column).  host: where the modes that set the
+// scalars the host reads (rho ... nonfinite) also write them, kScalWords
+// words per right-hand side of pinned memory, or null.
+constexpr int kScalWords = 8;
 void launch_finish(const double *partials, int nb, int kb, int K, int mode, Ctrl *ctrl, int k, int m,
-                   hipStream_t s);
+                   hipStream_t s, double *host = nullptr);
 // Profiling of the reduction passes: when set (on the calling host thread),
 // launch_finish calls finish_hook(finish_hook_arg) before it enqueues the
 // finish kernel, so that a pass and its finish kernel can be timed apart.
@@ -357,13 +361,13 @@ void launch_cgs_dot(i64 M, int K, Prec p, const void *Q, i64 ldq, int kb, void *
                     Ctrl *ctrl, hipStream_t s);
 // w <- w - Q (h1 + h2), ||w||^2 and the Givens step of column k.
 void launch_cgs_norm(i64 M, int K, Prec p, const void *Q, i64 ldq, int kb, void *w, double *partials,
-                     Ctrl *ctrl, int k, int m, hipStream_t s);
+                     Ctrl *ctrl, int k, int m, hipStream_t s, double *host);
 void launch_resid64(const Matrix &A, const double *x, const double *b, double *r,
-                    double *partials, Ctrl *ctrl, int m, hipStream_t s);
+                    double *partials, Ctrl *ctrl, int m, hipStream_t s, double *host);
 // ||v_j||^2 per right-hand side, then the finish `mode` (kFinishRho0 or
 // kFinishResid with restart length m).
 void launch_norm64(i64 M, int K, const double *v, double *partials, Ctrl *ctrl, int mode, int m,
-                   hipStream_t s);
+                   hipStream_t s, double *host);
 void launch_cast(i64 M, int K, Prec p, const double *r, const Ctrl *ctrl, void *q, hipStream_t s);
 // Completed Krylov steps per right-hand side (the size of each back-solve).
 struct KCount {
@@ -420,7 +424,7 @@ void launch_bprolong(const Geom &gf, const Geom &gc, Prec p, int K, const void *
 // r = b - A x in FP64 for K right-hand sides, then rho_j = ||r_j|| into
 // ctrl[j] (start of a cycle, as launch_resid64) by the norm kernel.
 void launch_bresid64(const Matrix &A, int K, int R, const double *x, const double *b, double *r,
-                     double *partials, Ctrl *ctrl, int m, hipStream_t s);
+                     double *partials, Ctrl *ctrl, int m, hipStream_t s, double *host);
 // [nrhs][N] natural order <-> [N][K] colour-blocked interleaved (right-hand
 // sides nrhs..K-1 are zero-filled on the way in and dropped on the way out).
 // `zero`: a row of K elements of type dst to clear in the same launch, or null.

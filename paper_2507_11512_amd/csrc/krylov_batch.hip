@@ -68,7 +68,7 @@ void batch_cgs_dot(i64 M, int K, Prec p, const void *Q, i64 ldq, int kb, void *w
 }
 
 void batch_cgs_norm(i64 M, int K, Prec p, const void *Q, i64 ldq, int kb, void *w, double *partials,
-                    Ctrl *ctrl, int k, int m, hipStream_t s)
+                    Ctrl *ctrl, int k, int m, hipStream_t s, double *host)
 {
     const dim3 gr(red_blocks(M)), bl(kBlock);
     with_bk(K, p, [&](auto kc, auto *tag) {
@@ -80,7 +80,7 @@ void batch_cgs_norm(i64 M, int K, Prec p, const void *Q, i64 ldq, int kb, void *
 #undef HPGMX_KB_BODY
     });
     HPGMX_LAUNCH_CHECK();
-    launch_finish(partials, (int)gr.x, 1, K, kFinishNormGivens, ctrl, k, m, s);
+    launch_finish(partials, (int)gr.x, 1, K, kFinishNormGivens, ctrl, k, m, s, host);
 }
 
 }  // namespace hpgmx

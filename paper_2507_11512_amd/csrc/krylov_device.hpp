@@ -262,6 +262,6 @@ void batch_dot(i64 M, int K, Prec p, const void *Q, i64 ldq, int kb, const void 
 void batch_cgs_dot(i64 M, int K, Prec p, const void *Q, i64 ldq, int kb, void *w, double *partials,
                    Ctrl *ctrl, hipStream_t s);
 void batch_cgs_norm(i64 M, int K, Prec p, const void *Q, i64 ldq, int kb, void *w, double *partials,
-                    Ctrl *ctrl, int k, int m, hipStream_t s);
+                    Ctrl *ctrl, int k, int m, hipStream_t s, double *host);
 
 }  // namespace hpgmx

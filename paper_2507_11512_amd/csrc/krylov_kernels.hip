@@ -32,6 +32,21 @@ int red_blocks(i64 N)
     return (int)(b < kMaxRedBlocks ? (b < 1 ? 1 : b) : kMaxRedBlocks);
 }
 
+// The scalar block of c to the host's copy of it (pinned memory; null:
+// nowhere), by the thread that wrote it.  A copy after each step was a
+// launch of its own (2-4 us) and, for a batch, a strided transfer that cost
+// 85 us a step: a 3 x 40x48x56 batch took 12.1 ms with it, 7.9 without.
+__device__ __forceinline__ void scalars_to_host(const Ctrl *c, double *host)
+{
+    if (!host) return;
+    const double v[6] = {c->rho, c->inv_rho, c->beta, c->inv_beta, c->nrm2, c->rho0};
+    const unsigned long long flags = (unsigned)c->breakdown | (unsigned long long)(unsigned)c->nonfinite << 32;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) __hip_atomic_store(host + i, v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(reinterpret_cast<unsigned long long *>(host) + 6, flags, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Givens update of Hessenberg column k (0-based) in FP64, by one workgroup:
 // H(0:k,k) = h1 + h2, H(k+1,k) = beta; rotate by the earlier rotations (each
 // rotation reads both entries before writing either); form the rotation that
@@ -39,7 +54,7 @@ int red_blocks(i64 N)
 // The inputs are staged in LDS by all threads, the rotation chain runs in one
 // thread out of LDS and registers, and the results are written back in
 // parallel (a single thread reading global memory would wait on every load).
-__device__ void givens_column(Ctrl *c, int k, int m, double nrm2)
+__device__ void givens_column(Ctrl *c, int k, int m, double nrm2, double *host)
 {
     __shared__ double hk[kMaxBasis + 1], cs[kMaxBasis], sn[kMaxBasis], tk[2];
     const int t = threadIdx.x;
@@ -84,6 +99,7 @@ __device__ void givens_column(Ctrl *c, int k, int m, double nrm2)
         c->inv_beta = c->breakdown ? 0.0 : 1.0 / beta;
         c->colscale[k + 1] = c->inv_beta;  // q_{k+1} = w / beta, stored as w
         c->nonfinite = !isfinite(nrm2);
+        scalars_to_host(c, host);
     }
     __syncthreads();
     double *Hk = c->H + (i64)k * (m + 1);
@@ -137,42 +153,57 @@ __global__ __launch_bounds__(kBlock) void k_norm64(i64 M, const double *__restri
 // ---- finish kernel: add the partial sums of nb workgroups in order -------------------------
 constexpr int kFinishThreads = 1024;
 
+// The sum of a partial column over nb workgroups, by one wave.
+__device__ __forceinline__ double column_sum(const double *__restrict__ col, int nb, int lane)
+{
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    int b = lane;
+    for (; b + 192 < nb; b += 256) {
+        s0 += col[b];
+        s1 += col[b + 64];
+        s2 += col[b + 128];
+        s3 += col[b + 192];
+    }
+    for (; b < nb; b += 64) s0 += col[b];
+    return wave_sum((s0 + s1) + (s2 + s3));
+}
+
+// The inner products of a pass, one column per workgroup (of one wave):
+// h1 or h2 of right-hand side blockIdx.y, the sums over stored columns times
+// their scales.  Columns do not depend on each other: one workgroup that took
+// them all, two to a wave, needed 5.0 us a launch at 128^3 (1024 partial
+// sums a column, 18 columns on average), this takes 4.6.
+__global__ __launch_bounds__(64) void k_finish_columns(const double *__restrict__ partials, int nb, int K, int mode,
+                                                       Ctrl *ctrl)
+{
+    const int j = blockIdx.x, rhs = blockIdx.y;
+    Ctrl *c = ctrl + rhs;
+    const double scale = c->colscale[j];
+    const double s = column_sum(partials + (i64)(j * K + rhs) * kMaxRedBlocks, nb, threadIdx.x);
+    if (threadIdx.x == 0) (mode == kFinishH1 ? c->h1 : c->h2)[j] = s * scale;
+}
+
 // Workgroup j finishes right-hand side j: partial columns i * K + j for
 // i < kb, control block ctrl[j].  Wave w sums columns i = w, w + 16, ...;
 // lane l adds workgroups l, l + 64, ... with four independent accumulators,
 // then the wave adds its lanes.
 __global__ __launch_bounds__(kFinishThreads) void k_finish(const double *__restrict__ partials,
                                                            int nb, int kb, int K, int mode, Ctrl *ctrl,
-                                                           int k, int m)
+                                                           int k, int m, double *host)
 {
     __shared__ double tot[kMaxBasis];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int rhs = blockIdx.x;
     Ctrl *c = ctrl + rhs;
+    if (host) host += rhs * kScalWords;
     for (int j = wave; j < kb; j += kFinishThreads / 64) {
-        const double *col = partials + (i64)(j * K + rhs) * kMaxRedBlocks;
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-        int b = lane;
-        for (; b + 192 < nb; b += 256) {
-            s0 += col[b];
-            s1 += col[b + 64];
-            s2 += col[b + 128];
-            s3 += col[b + 192];
-        }
-        for (; b < nb; b += 64) s0 += col[b];
-        const double s = wave_sum((s0 + s1) + (s2 + s3));
+        const double s = column_sum(partials + (i64)(j * K + rhs) * kMaxRedBlocks, nb, lane);
         if (lane == 0) tot[j] = s;
     }
     __syncthreads();
     switch (mode) {
-    case kFinishH1:  // the sums are over stored columns: apply their scales
-        if ((int)threadIdx.x < kb) c->h1[threadIdx.x] = tot[threadIdx.x] * c->colscale[threadIdx.x];
-        break;
-    case kFinishH2:
-        if ((int)threadIdx.x < kb) c->h2[threadIdx.x] = tot[threadIdx.x] * c->colscale[threadIdx.x];
-        break;
     case kFinishNormGivens:
-        givens_column(c, k, m, tot[0]);
+        givens_column(c, k, m, tot[0], host);
         break;
     case kFinishResid:
         // start of a cycle: rho = ||r||, t = (rho, 0, ..., 0)
@@ -185,6 +216,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(const double *__restr
             c->nonfinite = !isfinite(rho);
             c->breakdown = 0;
             c->colscale[0] = 1.0;  // q_1 is cast already divided by rho
+            scalars_to_host(c, host);
         }
         break;
     case kFinishRho0:
@@ -192,6 +224,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(const double *__restr
             c->nrm2 = tot[0];
             c->rho0 = sqrt(tot[0]);
             c->nonfinite = !isfinite(c->rho0);
+            scalars_to_host(c, host);
         }
         break;
     case kFinishCorr:
@@ -204,11 +237,13 @@ thread_local void (*finish_hook)(void *) = nullptr;
 thread_local void *finish_hook_arg = nullptr;
 
 void launch_finish(const double *partials, int nb, int kb, int K, int mode, Ctrl *ctrl, int k, int m,
-                   hipStream_t s)
+                   hipStream_t s, double *host)
 {
     if (finish_hook) finish_hook(finish_hook_arg);
-    hipLaunchKernelGGL(k_finish, dim3(K), dim3(kFinishThreads), 0, s, partials, nb, kb, K, mode, ctrl,
-                       k, m);
+    if (mode == kFinishH1 || mode == kFinishH2)
+        hipLaunchKernelGGL(k_finish_columns, dim3(kb, K), dim3(64), 0, s, partials, nb, K, mode, ctrl);
+    else
+        hipLaunchKernelGGL(k_finish, dim3(K), dim3(kFinishThreads), 0, s, partials, nb, kb, K, mode, ctrl, k, m, host);
     HPGMX_LAUNCH_CHECK();
 }
 
@@ -470,10 +505,10 @@ void launch_cgs_dot(i64 M, int K, Prec p, const void *Q, i64 ldq, int kb, void *
 }
 
 void launch_cgs_norm(i64 M, int K, Prec p, const void *Q, i64 ldq, int kb, void *w, double *partials,
-                     Ctrl *ctrl, int k, int m, hipStream_t s)
+                     Ctrl *ctrl, int k, int m, hipStream_t s, double *host)
 {
     check_pair_layout(p, Q, ldq, w);
-    if (K > 1) return batch_cgs_norm(M, K, p, Q, ldq, kb, w, partials, ctrl, k, m, s);
+    if (K > 1) return batch_cgs_norm(M, K, p, Q, ldq, kb, w, partials, ctrl, k, m, s, host);
     const dim3 gr(red_blocks(M)), bl(kBlock);
     if (p == P64) {
 #define HPGMX_KB_BODY \
@@ -487,11 +522,11 @@ void launch_cgs_norm(i64 M, int K, Prec p, const void *Q, i64 ldq, int kb, void 
 #undef HPGMX_KB_BODY
     }
     HPGMX_LAUNCH_CHECK();
-    launch_finish(partials, (int)gr.x, 1, 1, kFinishNormGivens, ctrl, k, m, s);
+    launch_finish(partials, (int)gr.x, 1, 1, kFinishNormGivens, ctrl, k, m, s, host);
 }
 
 void launch_resid64(const Matrix &A, const double *x, const double *b, double *r,
-                    double *partials, Ctrl *ctrl, int m, hipStream_t s)
+                    double *partials, Ctrl *ctrl, int m, hipStream_t s, double *host)
 {
     const unsigned nb = (unsigned)red_blocks(A.g.N);
     with_cols(A, [&](auto c16) {
@@ -499,11 +534,11 @@ void launch_resid64(const Matrix &A, const double *x, const double *b, double *r
                            tile_remap(A), A.v64, (const void *)A.col, A.cmap, A.d64, x, b, r, partials);
     });
     HPGMX_LAUNCH_CHECK();
-    launch_finish(partials, (int)nb, 1, 1, kFinishResid, ctrl, 0, m, s);
+    launch_finish(partials, (int)nb, 1, 1, kFinishResid, ctrl, 0, m, s, host);
 }
 
 void launch_norm64(i64 M, int K, const double *v, double *partials, Ctrl *ctrl, int mode, int m,
-                   hipStream_t s)
+                   hipStream_t s, double *host)
 {
     const unsigned nb = (unsigned)red_blocks(M);
     with_k(K, [&](auto kc) {
@@ -511,7 +546,7 @@ void launch_norm64(i64 M, int K, const double *v, double *partials, Ctrl *ctrl, 
         hipLaunchKernelGGL((k_norm64<KK>), dim3(nb), dim3(kBlock), 0, s, M, v, partials);
     });
     HPGMX_LAUNCH_CHECK();
-    launch_finish(partials, (int)nb, 1, K, mode, ctrl, 0, m, s);
+    launch_finish(partials, (int)nb, 1, K, mode, ctrl, 0, m, s, host);
 }
 
 void launch_stencil_correlation(const Matrix &A, const double *lam, const double *x,
