@@ -668,7 +668,7 @@ void read_scal(hpgmx_ctx *c, int K, const double *host, Scal *out)
 void ensure_scal_events(hpgmx_ctx *c)
 {
     for (auto &e : c->ev_scal)
-        if (!e) hip_check(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
+        if (!e) hip_check(hipEventCreateWithFlags(&e, hipEventDisableTiming | hipEventDisableSystemFence), "hipEventCreate");
 }
 
 void mark_scal(hpgmx_ctx *c, int slot) { hip_check(hipEventRecord(c->ev_scal[slot], c->stream), "hipEventRecord"); }

@@ -88,12 +88,20 @@ __device__ __forceinline__ float recip(int d) { return __builtin_amdgcn_rcpf((fl
 // The off-diagonal values through a buffer resource: a load takes a 32-bit
 // offset per lane, the slot's place in a scalar register and an immediate,
 // with no address arithmetic of its own, and a lane past the end reads 0.
+// 16-bit values stay in a register each until they are used: two to a
+// register, a load would wait for the one before it.
 template <typename V> struct SlotLoads {
+    using Raw = std::conditional_t<sizeof(V) == 2, unsigned, V>;
+    static __device__ __forceinline__ V value(Raw w)
+    {
+        if constexpr (sizeof(V) == 2) return __builtin_bit_cast(V, (unsigned short)w);
+        else return w;
+    }
     static constexpr int kStride = (int)sizeof(V) << kDefaultEllChunkLog2;  // bytes from slot to slot
     __amdgpu_buffer_rsrc_t rsrc;
     __device__ __forceinline__ SlotLoads(const V *v, unsigned bytes)
         : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<V *>(v), 0, (int)bytes, 0x00027000)) {}
-    __device__ __forceinline__ V at(int s, unsigned off) const
+    __device__ __forceinline__ Raw at(int s, unsigned off) const
     {
         const int imm = s * kStride % 4096, base = s * kStride - imm;
         if constexpr (sizeof(V) == 8) {
@@ -103,7 +111,7 @@ template <typename V> struct SlotLoads {
         } else if constexpr (sizeof(V) == 4) {
             return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)(off + imm), base, 0));
         } else {
-            return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)(off + imm), base, 0));
+            return (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)(off + imm), base, 0);
         }
     }
 };
@@ -139,7 +147,7 @@ template <int K> constexpr int kSweepR = K >= 2 ? 2 : 1;
 
 // One row's entries, loaded ahead of its relaxation.
 template <typename V, typename S, int R> struct SweepRow {
-    V a[kSlots];
+    typename SlotLoads<V>::Raw a[kSlots];
     Pack<S, R> r;
     V d;
     int cell;         // its own, times K, plus the right-hand side
@@ -214,7 +222,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(const SweepArgs P, cons
             } else {  // not read: adds 0
 #pragma unroll
                 for (int s = 0; s < kSlots; ++s)
-                    if (slot_flip(s) == f) E.a[s] = from_t<V>((T)0);
+                    if (slot_flip(s) == f) E.a[s] = 0;
             }
         }
     };
@@ -245,7 +253,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(const SweepArgs P, cons
 #pragma unroll
         for (int s = 0; s < kSlots; ++s)
 #pragma unroll
-            for (int i = 0; i < R; ++i) acc[i] = madd(to_t<T>(E.a[s]), to_t<T>(xv[s].v[i]), acc[i]);
+            for (int i = 0; i < R; ++i) acc[i] = madd(to_t<T>(SlotLoads<V>::value(E.a[s])), to_t<T>(xv[s].v[i]), acc[i]);
     };
 
     const int last = P.tail ? 8 : 7;
