@@ -471,12 +471,20 @@ void sweep_launch(const V *v, const V *d, const SweepArgs &P, int tiles, int thr
 
 }  // namespace
 
+// A tile of one cell fits the LDS in every form of the launch: either
+// direction, from zero or from old values, with the restriction (which
+// reaches further than the sweep alone).
 bool sweep_possible(const Matrix &A, int K, Prec p)
 {
     const Geom &g = A.g;
-    SweepArgs P;
-    return A.clog2 == kDefaultEllChunkLog2 && g.N * K < (1 << 22) &&
-           sweep_args(P, g, nullptr, 1, 1, true, false, false, 2) * K * (i64)vec_bytes(p) <= (i64)kSweepLds - 16;
+    if (A.clog2 != kDefaultEllChunkLog2 || g.N * K > (1 << 22)) return false;
+    for (int form = 0; form < 4; ++form) {
+        SweepArgs P;
+        const bool zero = form & 2;
+        const i64 cells = sweep_args(P, g, nullptr, 1, 1, form & 1, zero, false, zero ? 1 : 2);
+        if (cells * K * (i64)vec_bytes(p) > (i64)kSweepLds - 16) return false;
+    }
+    return true;
 }
 
 void launch_sweep(const Matrix &A, Prec p, int K, bool forward, bool skip_first, const void *r, const void *zin,
@@ -491,6 +499,7 @@ void launch_sweep(const Matrix &A, Prec p, int K, bool forward, bool skip_first,
     const int L = K / (K == 8 ? kSweepR<8> : K == 4 ? kSweepR<4> : K == 2 ? kSweepR<2> : 1);
     int n = 1, m = 1;
     const size_t lds = choose_tile(g, one, K, L, vec_bytes(p), n, m);
+    if (lds == 0) throw std::runtime_error("launch_sweep: no tile fits the LDS");
     sweep_args(P, g, gc, n, m, forward, zero, skip_first, tail);
     P.remap = tile_remap(A);
     P.bytes = (unsigned)(ell_entries(g.N, A.clog2) * (i64)(p == P64 ? 8 : p == P32 ? 4 : 2));

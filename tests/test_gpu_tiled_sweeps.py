@@ -29,9 +29,10 @@ def pair(hp, dims, **kw):
     return [hp.Problem(dims, beta=0.3, layout=lay, **kw) for lay in (None, {"pair_rows": 0})]
 
 
-# tile edges: one cell, fewer cells than a tile, odd extents in each direction, several tiles with a remainder, the
-# largest FP32 level, long and short x-lines
-DIMS = [(2, 2, 2), (3, 5, 4), (13, 9, 7), (2, 34, 3), (64, 3, 2), (37, 26, 51), (50, 38, 26), (100, 102, 102)]
+# tile edges: one cell, fewer cells than a tile, odd extents in each direction, several tiles with a remainder, tiles
+# of several row chunks, the largest level (2^22 rows; in FP64 beyond its largest), long and short x-lines
+DIMS = [(2, 2, 2), (3, 5, 4), (13, 9, 7), (2, 34, 3), (64, 3, 2), (37, 26, 51), (50, 38, 26), (100, 102, 102), (131, 70, 99),
+        (128, 256, 128)]
 
 
 @pytest.mark.parametrize("dims", DIMS)
@@ -73,8 +74,34 @@ def test_vcycle(hp, dims, levels, pre, post, coarsest, dtype, cols):
                 P.close()
 
 
+@pytest.mark.parametrize("dtype,nrhs,extents", [(0, 1, range(128, 240, 12)), (1, 1, range(256, 480, 24)),
+                                                 (5, 1, range(512, 960, 48)), (1, 8, range(24, 72, 4)),
+                                                 (0, 4, range(24, 72, 4))])
+def test_widest_lines(hp, dtype, nrhs, extents):
+    """Around the widest x-lines whose tiles fit the LDS: the forms of a sweep need different amounts of it (the
+    backward restriction most), and a level runs in tiles only if all of them fit."""
+    import torch
+    for nx in extents:
+        dims = (nx, 8, 12)
+        for sweep in ("forward", "backward", "symmetric"):
+            Ps = pair(hp, dims, levels=2, sweep=sweep)
+            try:
+                r = torch.stack([vec(dims, 70 + j, dtype) for j in range(nrhs)])
+                zs = [torch.full_like(r, float("nan")) for _ in Ps]
+                for P, z in zip(Ps, zs):
+                    if nrhs == 1:
+                        hp.vcycle(P.h, dtype, r[0], z[0])
+                    else:
+                        hp.vcycle_batched(P.h, dtype, r, z)
+                assert torch.isfinite(zs[0]).all() and torch.equal(zs[0], zs[1]), (nx, sweep)
+            finally:
+                for P in Ps:
+                    P.close()
+
+
 # interleaved right-hand sides: levels below and above what a workgroup can hold, odd extents
-@pytest.mark.parametrize("dims,levels", [((16, 12, 20), 3), ((40, 48, 56), 2), ((37, 26, 51), 1), ((64, 40, 48), 3)])
+@pytest.mark.parametrize("dims,levels", [((16, 12, 20), 3), ((40, 48, 56), 2), ((37, 26, 51), 1), ((64, 40, 48), 3),
+                                         ((112, 88, 72), 4)])
 @pytest.mark.parametrize("nrhs", [2, 3, 8])
 @pytest.mark.parametrize("dtype", [0, 1, 3])
 def test_batched(hp, dims, levels, nrhs, dtype):
