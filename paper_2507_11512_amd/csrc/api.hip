@@ -313,26 +313,25 @@ void *gathered_vector(hpgmx_ctx *c, i64 N, Prec p)
 // that fills one clears the entry of the level used.
 void *entry(void *v, i64 N, Prec p) { return (char *)v + (size_t)N * vec_bytes(p); }
 
-// Levels whose half-sweeps run as one launch each (launch_sweep): those
-// where a launch per colour is bound by latency, up to kSweepBytes bytes of
-// matrix values per slot (times right-hand sides).  Beyond it the halo rows
-// cost more than the launches: a 30-step cycle with 3 levels takes, with
-// colour launches and with tiles on level 0 too, 4457 and 3204 us at 24^3,
-// 5467 and 4205 at 64^3 and 7561 and 6238 at 96^3 in FP32 (0.9M rows), 6391
-// and 4788 at 64^3, 7593 and 7070 at 80^3 (0.5M) and 10170 either way at
-// 96^3 in FP64, where a 96 x 88 x 80 level in tiles lost 2 %.  Batches gain
-// over the same range (30 steps, 3 levels, colour launches and tiles: FP32
-// 2 x 32^3 6011 and 3633 us, 4 x 48^3 7084 and 5224, 8 x 48^3 8226 and 7643;
-// FP64 4 x 48^3 8761 and 7061), but with 16-bit matrices, whose vectors are
-// FP32, up to half the rows of an FP32 batch: 4 x 48^3 6756 and 5668, 8 x
-// 48^3 7789 and 8605.  A handle
-// with a pair_rows of its own gets the launches it asks for, and a profiled
-// solve the launches that are timed one by one.
-constexpr i64 kSweepBytes = 1 << 22;
+// Levels whose half-sweeps run as one launch each (launch_sweep), by their
+// rows times right-hand sides.  Small ones gain the launches' latency; larger
+// ones still gain, because a tile's matrix entries are its values alone and
+// its neighbours come from LDS, until the halo rows cost more.  A 30-step
+// cycle with 4 levels, colour launches and tiles on level 0 (times in us):
+// FP32 64^3 (3 levels) 5467 and 4205, 112^3 9966 and 8298, 128^3 12039 and
+// 10357, 160^3 19852 and 18595; bfloat16 160^3 17470 and 16770; FP64 96^3
+// 10698 and 9108, 112^3 14003 and 13589, but 128^3 17882 and 18273.  Batches:
+// FP32 2 x 96^3 8957 and 7434, 4 x 80^3 8782 and 8677, but 4 x 96^3 12312
+// and 14287; binary16 4 x 64^3 6335 and 5540, but 4 x 80^3 8699 and 8791;
+// FP64 2 x 80^3 9388 and 8639, but 2 x 96^3 13636 and 13944.  The lines lie
+// between these.  Larger levels keep the launches per colour, which read the
+// columns as they are stored.  A handle with a pair_rows of its own gets the
+// launches it asks for, and a profiled solve the launches that are timed one
+// by one.
 bool tiled_size(const Layout &lay, i64 N, int K, Prec p)
 {
-    const i64 vb = matrix_prec(p) == P64 ? 8 : matrix_prec(p) == P32 ? 4 : K > 1 ? 8 : 2;
-    return lay.pair_rows == kDefaultPairRows && N * K * vb <= kSweepBytes;
+    const i64 most = K == 1 ? (p == P64 ? 3 << 19 : 1 << 22) : (p == P64 ? 9 << 17 : 7 << 18);
+    return lay.pair_rows == kDefaultPairRows && N * K <= most;
 }
 bool tiled(const hpgmx_ctx *c, int l, Prec p, int K)
 {

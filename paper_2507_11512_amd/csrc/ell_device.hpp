@@ -219,11 +219,11 @@ __device__ __forceinline__ T ell_row_dot2(const V *__restrict__ offv, const void
     return acc;
 }
 
-// Largest level whose split sums are formed in one launch (k_spmv_split)
-// rather than in a launch per colour: up to the largest level whose sweeps
-// run in tiles.  It reads what the colour launches read; a 30-step cycle
-// takes 3204 instead of 3843 us at 24^3 and 6238 instead of 6675 at 96^3
-// in FP32.
+// Largest level (rows times right-hand sides) whose split sums, where the
+// sweep left none, are formed in one launch rather than in one per colour.  It
+// reads what those read; a 30-step cycle takes 3204 instead of 3843 us at
+// 24^3, 6613 instead of 7014 at 96^3 and 8351 instead of 8672 at 112^3 in
+// FP32; from 128^3 on the two are within 0.5 % (144^3: 14566 and 14544).
 constexpr i64 kSpmvOneLaunch = 1 << 21;
 
 // The slots E of launch_spmv_split per colour (none for the whole rows).
