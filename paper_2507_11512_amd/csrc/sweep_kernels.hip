@@ -43,7 +43,9 @@
 
 namespace hpgmx {
 
-constexpr int kSweepThreads = 512;        // at most; two waves per SIMD, 256 VGPRs each
+// Threads of a workgroup at most: a row and the next one take up to 128 VGPRs
+// (four waves per SIMD), in FP64 up to 256 (two).
+template <typename V> constexpr int sweep_threads() { return sizeof(V) == 8 ? 512 : 1024; }
 constexpr int kCus = 256;
 constexpr size_t kSweepLds = 144 * 1024;  // bytes of z a workgroup may hold (of the CU's 160 KiB)
 
@@ -159,7 +161,7 @@ template <typename V, typename S, int R> struct SweepRow {
 
 // K interleaved right-hand sides, R per lane (K / R lanes share a row).
 template <typename V, typename S, int K, int R>
-__global__ __launch_bounds__(kSweepThreads) void k_sweep(const SweepArgs P, const V *__restrict__ offv,
+__global__ __launch_bounds__(sweep_threads<V>()) void k_sweep(const SweepArgs P, const V *__restrict__ offv,
                                                          const V *__restrict__ diag, const S *__restrict__ r,
                                                          const S *__restrict__ zin, const S *__restrict__ zc,
                                                          S *__restrict__ zout, S *__restrict__ rc)
@@ -441,7 +443,7 @@ i64 sweep_lanes(const SweepArgs &P, int q, int n, int m, int L)
 // The tile whose workgroups, taken one per CU, have the fewest row chunks to
 // work through one after the other; of equal ones the smallest.  Returns the
 // LDS bytes of a workgroup.
-size_t choose_tile(const Geom &g, const SweepArgs &P, int K, int L, size_t vb, int &n, int &m)
+size_t choose_tile(const Geom &g, const SweepArgs &P, int K, int L, int threads, size_t vb, int &n, int &m)
 {
     i64 best = -1;
     size_t lds = 0;
@@ -451,7 +453,7 @@ size_t choose_tile(const Geom &g, const SweepArgs &P, int K, int L, size_t vb, i
             const size_t b = ((size_t)cells * K * vb + 15) / 16 * 16;
             if (b > kSweepLds) break;
             i64 items = 0;
-            for (int q = P.first; q < 8; ++q) items += (sweep_lanes(P, q, nn, mm, L) + kSweepThreads - 1) / kSweepThreads;
+            for (int q = P.first; q < 8; ++q) items += (sweep_lanes(P, q, nn, mm, L) + threads - 1) / threads;
             const i64 cost = (sweep_tiles(g, nn, mm) + kCus - 1) / kCus * items;
             if (best < 0 || cost < best) { best = cost; n = nn; m = mm; lds = b; }
         }
@@ -496,16 +498,17 @@ void launch_sweep(const Matrix &A, Prec p, int K, bool forward, bool skip_first,
     const Geom &g = A.g;
     SweepArgs one{}, P{};
     sweep_args(one, g, gc, 1, 1, forward, zero, skip_first, tail);
+    const int most = p == P64 ? sweep_threads<double>() : sweep_threads<float>();
     const int L = K / (K == 8 ? kSweepR<8> : K == 4 ? kSweepR<4> : K == 2 ? kSweepR<2> : 1);
     int n = 1, m = 1;
-    const size_t lds = choose_tile(g, one, K, L, vec_bytes(p), n, m);
+    const size_t lds = choose_tile(g, one, K, L, most, vec_bytes(p), n, m);
     if (lds == 0) throw std::runtime_error("launch_sweep: no tile fits the LDS");
     sweep_args(P, g, gc, n, m, forward, zero, skip_first, tail);
     P.remap = tile_remap(A);
     P.bytes = (unsigned)(ell_entries(g.N, A.clog2) * (i64)(p == P64 ? 8 : p == P32 ? 4 : 2));
     i64 lanes = 64;
     for (int q = P.first; q < 8; ++q) lanes = std::max(lanes, sweep_lanes(one, q, n, m, L));
-    const int threads = (int)std::min<i64>(kSweepThreads, (lanes + 63) / 64 * 64);
+    const int threads = (int)std::min<i64>(most, (lanes + 63) / 64 * 64);
     const int tiles = sweep_tiles(g, n, m);
     auto go = [&](auto *v, auto *d, auto sv) {
         using V = std::remove_const_t<std::remove_pointer_t<decltype(v)>>;
