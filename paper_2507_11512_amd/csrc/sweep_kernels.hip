@@ -25,9 +25,13 @@
 // one: 64^3 level 45 -> 12 us from zero with the restriction, 13.6 us with
 // the prolongation; 32^3 36 -> 10; 16^3 27 -> 8.  Solves of 16^3
 // (symmetric) 6.5 -> 3.4 ms, 48 x 40 x 32 9.9 -> 5.4 ms, 128^3 63 -> 52 ms.
-// Slower variants: columns loaded and mapped to LDS cells (18 us on every
-// size), scalar loads of each position's constants (+0.4 us a colour), half
-// of the waves loading while the other half relaxes (+20 %).
+// Where a tile's rows take one lane each, the waves split (SPLIT): while one
+// half relaxes its colour the other finds and loads the next, which took
+// solves of 16^3 from 3.2 to 2.8 ms, of 48 x 40 x 32 in binary16 from 5.1 to
+// 4.4 ms and a batch of 3 x 40x48x56 from 7.8 to 6.9 ms.  Slower variants:
+// columns loaded and mapped to LDS cells (18 us on every size), scalar loads
+// of each position's constants (+0.4 us a colour), split waves with several
+// row chunks each (+20 %: the registers spill).
 //
 // The tile's z lies in LDS with the same strides for every colour, each line
 // followed by a zero cell and the lines outside the grid zero, so a
@@ -160,7 +164,10 @@ template <typename V, typename S, int R> struct SweepRow {
 }  // namespace
 
 // K interleaved right-hand sides, R per lane (K / R lanes share a row).
-template <typename V, typename S, int K, int R>
+// SPLIT: a tile whose rows take one lane each at every position.  Half of the
+// waves relax the even positions, the others the odd ones, and each half
+// finds and loads its next rows while the other relaxes.
+template <typename V, typename S, int K, int R, bool SPLIT>
 __global__ __launch_bounds__(sweep_threads<V>()) void k_sweep(const SweepArgs P, const V *__restrict__ offv,
                                                          const V *__restrict__ diag, const S *__restrict__ r,
                                                          const S *__restrict__ zin, const S *__restrict__ zc,
@@ -173,6 +180,8 @@ __global__ __launch_bounds__(sweep_threads<V>()) void k_sweep(const SweepArgs P,
     extern __shared__ __align__(16) unsigned char smem[];
     S *zs = reinterpret_cast<S *>(smem);
     const int tid = threadIdx.x, nt = blockDim.x;
+    const int ng = SPLIT ? nt / 2 : nt;  // lanes that work on a position
+    const int group = SPLIT ? __builtin_amdgcn_readfirstlane(tid >= ng ? 1 : 0) : 0, gid = tid - group * ng;
     const int rhs = K > 1 ? tid % L * R : 0;
     const int tile = (int)xcd_tile(blockIdx.x, gridDim.x, P.remap);
     const int kt = tile / P.tj, K0 = kt * P.m, J0 = (tile - kt * P.tj) * P.n;
@@ -201,7 +210,7 @@ __global__ __launch_bounds__(sweep_threads<V>()) void k_sweep(const SweepArgs P,
         const unsigned q = word(pos);
         const int c = colour(pos), jn = q >> 4 & 31, jlo = (int)(q & 15) - 8, klo = (int)(q >> 9 & 15) - 8;
         const int kn = q >> 13 & 31;
-        const int t = (chunk * nt + tid) / L;
+        const int t = (SPLIT ? gid : chunk * nt + tid) / L;
         const int line = small_div(t, rbx), ii = t - __mul24(line, bxe);
         const int kq = small_div(line, recip(jn)), jr = jlo + (line - __mul24(kq, jn)), kr = klo + kq;
         const int jj = J0 + jr, kk = K0 + kr;
@@ -264,9 +273,8 @@ __global__ __launch_bounds__(sweep_threads<V>()) void k_sweep(const SweepArgs P,
         return (bxe * (int)(q >> 4 & 31) * (int)(q >> 13 & 31) * L + nt - 1) / nt;
     };
 
-    Row A, B;
-    int pos = P.first, chunk = 0, nchunks = chunks(pos);
-    fetch(pos, 0, A);
+    Row A;
+    fetch(P.first + group, 0, A);
 
     // z: the old values, or zero
     if (zin) {
@@ -296,46 +304,60 @@ __global__ __launch_bounds__(sweep_threads<V>()) void k_sweep(const SweepArgs P,
     }
     lds_barrier();
 
-    // one chunk of rows: E holds its entries, F takes those of the next one
-    auto step = [&](Row &E, Row &F) -> bool {
-        int npos = pos, nchunk = chunk + 1;
-        if (nchunk == nchunks) {
-            npos = pos + 1;
-            nchunk = 0;
-        }
-        // E was loaded during the chunk before: wait for it before the next
-        // loads go out, not behind them
-        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
-        sched_fence();
-        if (npos <= last) fetch(npos, nchunk, F);
-        sched_fence();
-        if (E.act) {
-            T acc[R];
-            Pack<S, R> out;
-            row_sum(pos, E, acc);
-            if (pos < 8) {
+    auto relax = [&](int pos, const Row &E) {
+                if (E.act) {
+                    T acc[R];
+                    Pack<S, R> out;
+                    row_sum(pos, E, acc);
+                    if (pos < 8) {
 #pragma unroll
-                for (int i = 0; i < R; ++i) out.v[i] = from_t<S>((to_t<T>(E.r.v[i]) - acc[i]) / to_t<T>(E.d));
-                stp<S, R>(zs + E.cell, out);
-            } else {  // the colour-4 block is the coarse level in its natural order
-                const Pack<S, R> own = ldp<S, R>(zs + E.cell);
+                        for (int i = 0; i < R; ++i) out.v[i] = from_t<S>((to_t<T>(E.r.v[i]) - acc[i]) / to_t<T>(E.d));
+                        stp<S, R>(zs + E.cell, out);
+                    } else {  // the colour-4 block is the coarse level in its natural order
+                        const Pack<S, R> own = ldp<S, R>(zs + E.cell);
 #pragma unroll
-                for (int i = 0; i < R; ++i)
-                    out.v[i] = from_t<S>(P.tail == 1 ? -acc[i]
-                                                     : to_t<T>(E.r.v[i]) - (to_t<T>(E.d) * to_t<T>(own.v[i]) + acc[i]));
-                stp<S, R>(rc + ((i64)coarse_index(P, E.ii, E.jj, E.kk) * K + rhs), out);
-            }
-        }
-        if (npos > last) return true;
-        if (npos != pos) {
-            lds_barrier();
-            nchunks = chunks(npos);
-        }
-        pos = npos;
-        chunk = nchunk;
-        return false;
+                        for (int i = 0; i < R; ++i)
+                            out.v[i] = from_t<S>(P.tail == 1 ? -acc[i]
+                                                             : to_t<T>(E.r.v[i]) - (to_t<T>(E.d) * to_t<T>(own.v[i]) + acc[i]));
+                        stp<S, R>(rc + ((i64)coarse_index(P, E.ii, E.jj, E.kk) * K + rhs), out);
+                    }
+                }
     };
-    while (!step(A, B) && !step(B, A)) {}
+    if constexpr (SPLIT) {
+        for (int pos = P.first;; ++pos) {
+            if (((pos - P.first) & 1) == group) relax(pos, A);
+            else if (pos < last) fetch(pos + 1, 0, A);
+            if (pos == last) break;
+            lds_barrier();
+        }
+    } else {
+        Row B;
+        int pos = P.first, chunk = 0, nchunks = chunks(pos);
+        // one chunk of rows: E holds its entries, F takes those of the next one
+        auto step = [&](Row &E, Row &F) -> bool {
+            int npos = pos, nchunk = chunk + 1;
+            if (nchunk == nchunks) {
+                npos = pos + 1;
+                nchunk = 0;
+            }
+            // E was loaded during the chunk before: wait for it before the next
+            // loads go out, not behind them
+            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+            sched_fence();
+            if (npos <= last) fetch(npos, nchunk, F);
+            sched_fence();
+            relax(pos, E);
+            if (npos > last) return true;
+            if (npos != pos) {
+                lds_barrier();
+                nchunks = chunks(npos);
+            }
+            pos = npos;
+            chunk = nchunk;
+            return false;
+        };
+        while (!step(A, B) && !step(B, A)) {}
+    }
     if (!P.tail) lds_barrier();
 
     // the tile's own rows
@@ -440,9 +462,10 @@ i64 sweep_lanes(const SweepArgs &P, int q, int n, int m, int L)
     return (i64)(P.nx1 >> 1) * ((P.pos[q] >> 4 & 31) - 1 + n) * ((P.pos[q] >> 13 & 31) - 1 + m) * L;
 }
 
-// The tile whose workgroups, taken one per CU, have the fewest row chunks to
-// work through one after the other; of equal ones the smallest.  Returns the
-// LDS bytes of a workgroup.
+// The tile whose workgroups, taken one per CU, have the least to work through
+// one after the other: row chunks, which take a sixth less time where the
+// waves can split (k_sweep); of equal ones the smallest.  Returns the LDS
+// bytes of a workgroup.
 size_t choose_tile(const Geom &g, const SweepArgs &P, int K, int L, int threads, size_t vb, int &n, int &m)
 {
     i64 best = -1;
@@ -452,22 +475,26 @@ size_t choose_tile(const Geom &g, const SweepArgs &P, int K, int L, int threads,
             const i64 cells = 1 + (i64)8 * P.sx * (P.pj - 1 + nn) * (P.pk - 1 + mm);
             const size_t b = ((size_t)cells * K * vb + 15) / 16 * 16;
             if (b > kSweepLds) break;
-            i64 items = 0;
-            for (int q = P.first; q < 8; ++q) items += (sweep_lanes(P, q, nn, mm, L) + threads - 1) / threads;
-            const i64 cost = (sweep_tiles(g, nn, mm) + kCus - 1) / kCus * items;
+            i64 items = 0, most = 0;
+            for (int q = P.first; q < 8; ++q) {
+                const i64 lanes = sweep_lanes(P, q, nn, mm, L);
+                items += (lanes + threads - 1) / threads;
+                most = std::max(most, lanes);
+            }
+            const i64 cost = (sweep_tiles(g, nn, mm) + kCus - 1) / kCus * items * (most <= threads / 2 ? 5 : 6);
             if (best < 0 || cost < best) { best = cost; n = nn; m = mm; lds = b; }
         }
     return lds;
 }
 
-template <typename V, typename S, int K>
+template <typename V, typename S, int K, bool SPLIT>
 void sweep_launch(const V *v, const V *d, const SweepArgs &P, int tiles, int threads, size_t lds, const void *r,
                   const void *zin, const void *zc, void *zout, void *rc, hipStream_t s)
 {
-    if (lds > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sweep<V, S, K, kSweepR<K>>),
+    if (lds > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sweep<V, S, K, kSweepR<K>, SPLIT>),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         throw std::runtime_error("launch_sweep: the device refuses the workgroup's LDS");
-    hipLaunchKernelGGL((k_sweep<V, S, K, kSweepR<K>>), dim3(tiles), dim3(threads), lds, s, P, v, d, (const S *)r, (const S *)zin,
+    hipLaunchKernelGGL((k_sweep<V, S, K, kSweepR<K>, SPLIT>), dim3(tiles), dim3(threads), lds, s, P, v, d, (const S *)r, (const S *)zin,
                        (const S *)zc, (S *)zout, (S *)rc);
 }
 
@@ -508,16 +535,23 @@ void launch_sweep(const Matrix &A, Prec p, int K, bool forward, bool skip_first,
     P.bytes = (unsigned)(ell_entries(g.N, A.clog2) * (i64)(p == P64 ? 8 : p == P32 ? 4 : 2));
     i64 lanes = 64;
     for (int q = P.first; q < 8; ++q) lanes = std::max(lanes, sweep_lanes(one, q, n, m, L));
-    const int threads = (int)std::min<i64>(most, (lanes + 63) / 64 * 64);
+    const bool split = lanes <= most / 2;  // both halves of the waves fit
+    const int threads = (int)std::min<i64>(most, (lanes + 63) / 64 * 64 * (split ? 2 : 1));
     const int tiles = sweep_tiles(g, n, m);
-    auto go = [&](auto *v, auto *d, auto sv) {
+    auto go2 = [&](auto kc, auto *v, auto *d, auto sv) {
         using V = std::remove_const_t<std::remove_pointer_t<decltype(v)>>;
         using S = decltype(sv);
-        if (K == 1) sweep_launch<V, S, 1>(v, d, P, tiles, threads, lds, r, zin, zc, zout, rc, s);
+        constexpr int KK = decltype(kc)::value;
+        if (split) sweep_launch<V, S, KK, true>(v, d, P, tiles, threads, lds, r, zin, zc, zout, rc, s);
+        else sweep_launch<V, S, KK, false>(v, d, P, tiles, threads, lds, r, zin, zc, zout, rc, s);
+    };
+    auto go = [&](auto *v, auto *d, auto sv) {
+        using S = decltype(sv);
+        if (K == 1) go2(std::integral_constant<int, 1>{}, v, d, S{});
         else if constexpr (!std::is_same<S, __half>::value && !std::is_same<S, bf16>::value) {
-            if (K == 2) sweep_launch<V, S, 2>(v, d, P, tiles, threads, lds, r, zin, zc, zout, rc, s);
-            else if (K == 4) sweep_launch<V, S, 4>(v, d, P, tiles, threads, lds, r, zin, zc, zout, rc, s);
-            else if (K == 8) sweep_launch<V, S, 8>(v, d, P, tiles, threads, lds, r, zin, zc, zout, rc, s);
+            if (K == 2) go2(std::integral_constant<int, 2>{}, v, d, S{});
+            else if (K == 4) go2(std::integral_constant<int, 4>{}, v, d, S{});
+            else if (K == 8) go2(std::integral_constant<int, 8>{}, v, d, S{});
             else throw std::runtime_error("launch_sweep: unsupported batch width");
         } else throw std::runtime_error("launch_sweep: no batches of the 16-bit hierarchy");
     };
