@@ -464,6 +464,44 @@ static inline unsigned grid_for(i64 n) { return (unsigned)((n + kBlock - 1) / kB
         if (e_ != hipSuccess) throw std::runtime_error(hipGetErrorString(e_));  \
     } while (0)
 
+// ---- sums across a wavefront ----------------------------------------------------------
+// v plus the value O lanes away (lane xor O), for O = 32, 16, 8, 4, 2, 1 in
+// this order: from O = 4 on the partner is taken a rotation away, which after
+// the steps before holds the same value.  Register moves (the gfx950 half and
+// row swaps, DPP) instead of __shfl_xor, which is two LDS permutes per
+// accumulator and step (14 columns: 168 a wave): on 61440 rows the first
+// GEMVT took 7.5 us with those and takes 5.6, the update pass 4.7 and 3.0;
+// the 48 x 40 x 32 binary16 solve 4.37 -> 4.02 ms, a 3 x 40x48x56 batch 6.93 ->
+// 6.53 ms, a 320^3 cycle 126.8 -> 126.5 ms.
+template <int O> __device__ __forceinline__ double add_xor(double v)
+{
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    if constexpr (O == 32 || O == 16) {
+        const auto l = O == 32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                               : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        const auto h = O == 32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                               : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    } else {
+        // row rotations by 8 and 4 lanes, quad permutes for 2 and 1
+        constexpr int dpp = O == 8 ? 0x128 : O == 4 ? 0x124 : O == 2 ? 0x4e : 0xb1;
+        const int l = __builtin_amdgcn_mov_dpp((int)lo, dpp, 0xf, 0xf, true);
+        const int h = __builtin_amdgcn_mov_dpp((int)hi, dpp, 0xf, 0xf, true);
+        return v + __hiloint2double(h, l);
+    }
+}
+// The sum over the lanes with equal lane % L, in every lane.
+template <int L> __device__ __forceinline__ double lane_sum(double v)
+{
+    v = add_xor<32>(v);
+    v = add_xor<16>(v);
+    if constexpr (L <= 8) v = add_xor<8>(v);
+    if constexpr (L <= 4) v = add_xor<4>(v);
+    if constexpr (L <= 2) v = add_xor<2>(v);
+    if constexpr (L <= 1) v = add_xor<1>(v);
+    return v;
+}
+
 // ---- deterministic block partial sums ----------------------------------------------
 // Lane l of a launch holds NA accumulators acc[a]; lanes with equal l % L
 // (L divides 64) belong together.  The workgroup's sum of acc[a] over the
@@ -480,9 +518,7 @@ __device__ __forceinline__ void store_partials_g(const double (&acc)[NA], int na
 #pragma unroll
     for (int a = 0; a < NA; ++a) {
         if (a < na) {
-            double v = acc[a];
-#pragma unroll
-            for (int o = 32; o >= L; o >>= 1) v += __shfl_xor(v, o, 64);
+            const double v = lane_sum<L>(acc[a]);
             if (lane < L) red[wave][a * L + lane] = v;
         }
     }
