@@ -25,6 +25,7 @@
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -174,8 +175,12 @@ struct ColMap {
 };
 ColMap make_colmap(const Geom &g);
 
+struct SweepPlans;  // launch parameters of a level's tiled sweeps (sweep_kernels.hip)
 struct Matrix {
     Geom g;
+    // filled as the forms are first used; belongs to the handle, like the
+    // level itself (a handle is used by one thread at a time)
+    mutable std::shared_ptr<SweepPlans> sweeps;
     int clog2 = 0;         // ELL chunking (see ell_row)
     int order = kRemapSlab;   // tile order of its launches (Layout::order)
     bool c16 = false;         // column format: int32 indices, or 16-bit offsets

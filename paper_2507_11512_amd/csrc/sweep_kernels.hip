@@ -42,6 +42,8 @@
 #include "ell_device.hpp"
 
 #include <algorithm>
+#include <map>
+#include <memory>
 #include <stdexcept>
 #include <type_traits>
 
@@ -500,44 +502,89 @@ void sweep_launch(const V *v, const V *d, const SweepArgs &P, int tiles, int thr
 
 }  // namespace
 
+// One form of a level's sweep, ready to launch.  Working it out takes the host
+// 4-6 us, as long as the launch itself and longer than the launch leaves it on
+// a small level, so it is kept (16^3 symmetric solve from the host 2.78 ->
+// 2.49 ms).
+struct SweepPlan {
+    SweepArgs P{};
+    int tiles = 0, threads = 0;
+    bool split = false;
+    size_t lds = 0;
+};
+struct SweepPlans {
+    std::map<unsigned, SweepPlan> form;
+    std::map<unsigned, bool> possible;
+};
+
+static SweepPlans &plans_of(const Matrix &A)
+{
+    if (!A.sweeps) A.sweeps = std::make_shared<SweepPlans>();
+    return *A.sweeps;
+}
+
 // A tile of one cell fits the LDS in every form of the launch: either
 // direction, from zero or from old values, with the restriction (which
 // reaches further than the sweep alone).
-bool sweep_possible(const Matrix &A, int K, Prec p)
+static bool fits_lds(const Matrix &A, int K, Prec p)
 {
-    const Geom &g = A.g;
-    if (A.clog2 != kDefaultEllChunkLog2 || g.N * K > (1 << 22)) return false;
     for (int form = 0; form < 4; ++form) {
         SweepArgs P;
         const bool zero = form & 2;
-        const i64 cells = sweep_args(P, g, nullptr, 1, 1, form & 1, zero, false, zero ? 1 : 2);
+        const i64 cells = sweep_args(P, A.g, nullptr, 1, 1, form & 1, zero, false, zero ? 1 : 2);
         if (cells * K * (i64)vec_bytes(p) > (i64)kSweepLds - 16) return false;
     }
     return true;
 }
 
+bool sweep_possible(const Matrix &A, int K, Prec p)
+{
+    if (A.clog2 != kDefaultEllChunkLog2 || A.g.N * K > (1 << 22)) return false;
+    auto &known = plans_of(A).possible;
+    const unsigned key = (unsigned)K << 4 | (unsigned)p;
+    const auto it = known.find(key);
+    return it != known.end() ? it->second : known.emplace(key, fits_lds(A, K, p)).first->second;
+}
+
+static SweepPlan make_plan(const Matrix &A, Prec p, int K, const Geom *gc, bool forward, bool zero, bool skip_first,
+                           int tail)
+{
+    const Geom &g = A.g;
+    SweepPlan o;
+    SweepArgs one{};
+    sweep_args(one, g, gc, 1, 1, forward, zero, skip_first, tail);
+    const int most = p == P64 ? sweep_threads<double>() : sweep_threads<float>();
+    const int L = K / (K == 8 ? kSweepR<8> : K == 4 ? kSweepR<4> : K == 2 ? kSweepR<2> : 1);
+    int n = 1, m = 1;
+    o.lds = choose_tile(g, one, K, L, most, vec_bytes(p), n, m);
+    if (o.lds == 0) throw std::runtime_error("launch_sweep: no tile fits the LDS");
+    sweep_args(o.P, g, gc, n, m, forward, zero, skip_first, tail);
+    o.P.remap = tile_remap(A);
+    o.P.bytes = (unsigned)(ell_entries(g.N, A.clog2) * (i64)(p == P64 ? 8 : p == P32 ? 4 : 2));
+    i64 lanes = 64;
+    for (int q = o.P.first; q < 8; ++q) lanes = std::max(lanes, sweep_lanes(one, q, n, m, L));
+    o.split = lanes <= most / 2;  // both halves of the waves fit
+    o.threads = (int)std::min<i64>(most, (lanes + 63) / 64 * 64 * (o.split ? 2 : 1));
+    o.tiles = sweep_tiles(g, n, m);
+    return o;
+}
+
+// gc is the level below A in every call, so it is no part of the key.
 void launch_sweep(const Matrix &A, Prec p, int K, bool forward, bool skip_first, const void *r, const void *zin,
                   const Geom *gc, const void *zc, void *zout, void *rc, hipStream_t s)
 {
     if (!sweep_possible(A, K, p)) throw std::runtime_error("launch_sweep: level too large");
     const bool zero = zin == nullptr;
     const int tail = !rc ? 0 : zero ? 1 : 2;
-    const Geom &g = A.g;
-    SweepArgs one{}, P{};
-    sweep_args(one, g, gc, 1, 1, forward, zero, skip_first, tail);
-    const int most = p == P64 ? sweep_threads<double>() : sweep_threads<float>();
-    const int L = K / (K == 8 ? kSweepR<8> : K == 4 ? kSweepR<4> : K == 2 ? kSweepR<2> : 1);
-    int n = 1, m = 1;
-    const size_t lds = choose_tile(g, one, K, L, most, vec_bytes(p), n, m);
-    if (lds == 0) throw std::runtime_error("launch_sweep: no tile fits the LDS");
-    sweep_args(P, g, gc, n, m, forward, zero, skip_first, tail);
-    P.remap = tile_remap(A);
-    P.bytes = (unsigned)(ell_entries(g.N, A.clog2) * (i64)(p == P64 ? 8 : p == P32 ? 4 : 2));
-    i64 lanes = 64;
-    for (int q = P.first; q < 8; ++q) lanes = std::max(lanes, sweep_lanes(one, q, n, m, L));
-    const bool split = lanes <= most / 2;  // both halves of the waves fit
-    const int threads = (int)std::min<i64>(most, (lanes + 63) / 64 * 64 * (split ? 2 : 1));
-    const int tiles = sweep_tiles(g, n, m);
+    const unsigned key = (unsigned)K << 9 | (unsigned)p << 5 | (unsigned)tail << 3 | (unsigned)forward << 2 |
+                         (unsigned)zero << 1 | (unsigned)skip_first;
+    auto &plans = plans_of(A).form;
+    auto it = plans.find(key);
+    if (it == plans.end()) it = plans.emplace(key, make_plan(A, p, K, gc, forward, zero, skip_first, tail)).first;
+    const SweepArgs &P = it->second.P;
+    const int tiles = it->second.tiles, threads = it->second.threads;
+    const bool split = it->second.split;
+    const size_t lds = it->second.lds;
     auto go2 = [&](auto kc, auto *v, auto *d, auto sv) {
         using V = std::remove_const_t<std::remove_pointer_t<decltype(v)>>;
         using S = decltype(sv);
