@@ -241,7 +241,7 @@ __global__ __launch_bounds__(sweep_threads<V>()) void k_sweep(const SweepArgs P,
     };
 
     // sum over the slots of a z, the z gathered from LDS, in slot order
-    auto row_sum = [&](int pos, const Row &E, T (&acc)[R]) {
+    auto row_sum = [&](auto masked, int pos, const Row &E, T (&acc)[R]) {
         const int c = colour(pos);
         // cell of the neighbour minus the row's own: an even line's (or
         // plane's) neighbours are the odd ones of the cell before and of its
@@ -260,6 +260,17 @@ __global__ __launch_bounds__(sweep_threads<V>()) void k_sweep(const SweepArgs P,
             xv[s] = ldp<S, R>(x);
             if (g != 4) xv[s + 1] = ldp<S, R>(zs + at);
             xv[g == 4 ? s + 1 : s + 2] = ldp<S, R>(x + K);
+        }
+        // the restriction after a sweep from zero leaves out slots whose z is
+        // not zero (at the other positions such cells still hold zero): they
+        // must add 0 also where that z is infinite or not a number
+        if constexpr (decltype(masked)::value) {
+            const unsigned q = word(8);
+#pragma unroll
+            for (int s = 0; s < kSlots; ++s)
+                if (!(q >> (17 + slot_flip(s)) & 1u))
+#pragma unroll
+                    for (int i = 0; i < R; ++i) xv[s].v[i] = from_t<S>((T)0);
         }
 #pragma unroll
         for (int i = 0; i < R; ++i) acc[i] = (T)0;
@@ -307,23 +318,24 @@ __global__ __launch_bounds__(sweep_threads<V>()) void k_sweep(const SweepArgs P,
     lds_barrier();
 
     auto relax = [&](int pos, const Row &E) {
-                if (E.act) {
-                    T acc[R];
-                    Pack<S, R> out;
-                    row_sum(pos, E, acc);
-                    if (pos < 8) {
+        if (E.act) {
+            T acc[R];
+            Pack<S, R> out;
+            if (pos < 8) {
+                row_sum(std::false_type{}, pos, E, acc);
 #pragma unroll
-                        for (int i = 0; i < R; ++i) out.v[i] = from_t<S>((to_t<T>(E.r.v[i]) - acc[i]) / to_t<T>(E.d));
-                        stp<S, R>(zs + E.cell, out);
-                    } else {  // the colour-4 block is the coarse level in its natural order
-                        const Pack<S, R> own = ldp<S, R>(zs + E.cell);
+                for (int i = 0; i < R; ++i) out.v[i] = from_t<S>((to_t<T>(E.r.v[i]) - acc[i]) / to_t<T>(E.d));
+                stp<S, R>(zs + E.cell, out);
+            } else {  // the colour-4 block is the coarse level in its natural order
+                row_sum(std::true_type{}, pos, E, acc);
+                const Pack<S, R> own = ldp<S, R>(zs + E.cell);
 #pragma unroll
-                        for (int i = 0; i < R; ++i)
-                            out.v[i] = from_t<S>(P.tail == 1 ? -acc[i]
-                                                             : to_t<T>(E.r.v[i]) - (to_t<T>(E.d) * to_t<T>(own.v[i]) + acc[i]));
-                        stp<S, R>(rc + ((i64)coarse_index(P, E.ii, E.jj, E.kk) * K + rhs), out);
-                    }
-                }
+                for (int i = 0; i < R; ++i)
+                    out.v[i] = from_t<S>(P.tail == 1 ? -acc[i]
+                                                     : to_t<T>(E.r.v[i]) - (to_t<T>(E.d) * to_t<T>(own.v[i]) + acc[i]));
+                stp<S, R>(rc + ((i64)coarse_index(P, E.ii, E.jj, E.kk) * K + rhs), out);
+            }
+        }
     };
     if constexpr (SPLIT) {
         for (int pos = P.first;; ++pos) {

@@ -74,6 +74,27 @@ def test_vcycle(hp, dims, levels, pre, post, coarsest, dtype, cols):
                 P.close()
 
 
+@pytest.mark.parametrize("dtype", [0, 1, 4])
+def test_not_finite(hp, dtype):
+    """Infinities and NaN spread as they do through the colour launches (padded and skipped slots add nothing)."""
+    import torch
+    dims = (24, 20, 16)
+    for sweep in ("forward", "backward", "symmetric"):
+        Ps = pair(hp, dims, levels=3, sweep=sweep)
+        try:
+            for at, v in ((0, "inf"), (3001, "nan"), (3000, "-inf"), (24 * 20 * 16 - 1, "nan")):
+                r = vec(dims, 50, dtype)
+                r[at] = float(v)
+                zs = [torch.zeros_like(r) for _ in Ps]
+                for P, z in zip(Ps, zs):
+                    hp.vcycle(P.h, dtype, r, z)
+                assert torch.equal(zs[0].isnan(), zs[1].isnan()), (sweep, at)
+                assert torch.equal(zs[0].nan_to_num(), zs[1].nan_to_num()), (sweep, at)
+        finally:
+            for P in Ps:
+                P.close()
+
+
 @pytest.mark.parametrize("dtype,nrhs,extents", [(0, 1, range(128, 240, 12)), (1, 1, range(256, 480, 24)),
                                                  (5, 1, range(512, 960, 48)), (1, 8, range(24, 72, 4)),
                                                  (0, 4, range(24, 72, 4))])
