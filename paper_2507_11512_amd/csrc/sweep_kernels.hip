@@ -241,7 +241,7 @@ __global__ __launch_bounds__(sweep_threads<V>()) void k_sweep(const SweepArgs P,
     };
 
     // sum over the slots of a z, the z gathered from LDS, in slot order
-    auto row_sum = [&](auto masked, int pos, const Row &E, T (&acc)[R]) {
+    auto row_sum = [&](int pos, const Row &E, T (&acc)[R]) {
         const int c = colour(pos);
         // cell of the neighbour minus the row's own: an even line's (or
         // plane's) neighbours are the odd ones of the cell before and of its
@@ -261,23 +261,39 @@ __global__ __launch_bounds__(sweep_threads<V>()) void k_sweep(const SweepArgs P,
             if (g != 4) xv[s + 1] = ldp<S, R>(zs + at);
             xv[g == 4 ? s + 1 : s + 2] = ldp<S, R>(x + K);
         }
-        // the restriction after a sweep from zero leaves out slots whose z is
-        // not zero (at the other positions such cells still hold zero): they
-        // must add 0 also where that z is infinite or not a number
-        if constexpr (decltype(masked)::value) {
-            const unsigned q = word(8);
-#pragma unroll
-            for (int s = 0; s < kSlots; ++s)
-                if (!(q >> (17 + slot_flip(s)) & 1u))
-#pragma unroll
-                    for (int i = 0; i < R; ++i) xv[s].v[i] = from_t<S>((T)0);
-        }
 #pragma unroll
         for (int i = 0; i < R; ++i) acc[i] = (T)0;
 #pragma unroll
         for (int s = 0; s < kSlots; ++s)
 #pragma unroll
             for (int i = 0; i < R; ++i) acc[i] = madd(to_t<T>(SlotLoads<V>::value(E.a[s])), to_t<T>(xv[s].v[i]), acc[i]);
+    };
+
+    // The restriction after a sweep from zero leaves out slots whose z is not
+    // zero (at the other positions such cells still hold zero): row_sum adds 0
+    // times it, which is not 0 where it is infinite or not a number.  A sum
+    // that is not a number is formed again from the position's slots alone, in
+    // the same order.
+    auto skip_not_finite = [&](const Row &E, T (&acc)[R]) {
+        bool bad = false;
+#pragma unroll
+        for (int i = 0; i < R; ++i) bad = bad || acc[i] != acc[i];
+        if (!bad) return;
+        const unsigned q = word(8);
+        const int p = (int)word(16 + 4) + E.ii + ext_x(4) * (E.jj + ext_y(4) * E.kk);
+#pragma unroll
+        for (int i = 0; i < R; ++i) acc[i] = (T)0;
+#pragma unroll 1
+        for (int s = 0; s < kSlots; ++s) {
+            if (!(q >> (17 + slot_flip(s)) & 1u)) continue;
+            const int t = s < 13 ? s : s + 1, di = t % 3 - 1, dj = (t / 3) % 3 - 1, dk = t / 9 - 1;
+            // colour 4 lies on even lines and planes
+            const int at = E.cell + ((di ? block + (di < 0 ? -1 : 0) : 0) + (dj ? 2 * block - (dj < 0 ? P.sx : 0) : 0) +
+                                     (dk ? -4 * block - (dk < 0 ? plane : 0) : 0)) * K;
+            const T a = to_t<T>(offv[(i64)(p / (int)kChunk) * (kSlots * kChunk) + s * kChunk + p % (int)kChunk]);
+#pragma unroll
+            for (int i = 0; i < R; ++i) acc[i] = madd(a, to_t<T>(zs[at + i]), acc[i]);
+        }
     };
 
     const int last = P.tail ? 8 : 7;
@@ -321,13 +337,13 @@ __global__ __launch_bounds__(sweep_threads<V>()) void k_sweep(const SweepArgs P,
         if (E.act) {
             T acc[R];
             Pack<S, R> out;
+            row_sum(pos, E, acc);
             if (pos < 8) {
-                row_sum(std::false_type{}, pos, E, acc);
 #pragma unroll
                 for (int i = 0; i < R; ++i) out.v[i] = from_t<S>((to_t<T>(E.r.v[i]) - acc[i]) / to_t<T>(E.d));
                 stp<S, R>(zs + E.cell, out);
             } else {  // the colour-4 block is the coarse level in its natural order
-                row_sum(std::true_type{}, pos, E, acc);
+                if (P.tail == 1) skip_not_finite(E, acc);
                 const Pack<S, R> own = ldp<S, R>(zs + E.cell);
 #pragma unroll
                 for (int i = 0; i < R; ++i)
