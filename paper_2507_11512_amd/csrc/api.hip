@@ -643,6 +643,15 @@ struct Scal {  // mirrors the scalar block of Ctrl
 // memory, kScalWords words each, slot 0 or 1 of `host`.
 double *scal_slot(double *host, int K, int slot) { return host + (size_t)slot * K * kScalWords; }
 
+// Coherent memory, whose device stores no cache holds back: what a finish
+// kernel has released (scalars_to_host) the host reads behind its event.
+double *alloc_scal(int K)
+{
+    void *p = nullptr;
+    hip_check(hipHostMalloc(&p, (size_t)2 * K * kScalWords * sizeof(double), hipHostMallocCoherent), "hipHostMalloc");
+    return (double *)p;
+}
+
 void copy_scal(const double *from, int K, Scal *out)
 {
     for (int j = 0; j < K; ++j) std::memcpy(out + j, from + (size_t)j * kScalWords, sizeof(Scal));
@@ -664,6 +673,8 @@ void read_scal(hpgmx_ctx *c, int K, const double *host, Scal *out)
 // column k + 2, which the back-solve and the basis combination of a cycle
 // of k + 1 steps never read, and the next cycle starts afresh.  No step is
 // enqueued past the restart length or the iteration limit.
+// The events are recorded without a system fence: the kernel that writes the
+// scalars ends in one (scalars_to_host).
 void ensure_scal_events(hpgmx_ctx *c)
 {
     for (auto &e : c->ev_scal)
@@ -945,8 +956,7 @@ Batch &ensure_batch(hpgmx_ctx *c, int K)
     B.ctrl = (Ctrl *)c->dalloc(K * sizeof(Ctrl));
     hip_check(hipMemsetAsync(B.ctrl, 0, K * sizeof(Ctrl), c->stream), "hipMemsetAsync");
     B.partials = (double *)c->dalloc((size_t)kMaxRedBlocks * kMaxBasis * K * 8);
-    if (!B.host_scal)
-        hip_check(hipHostMalloc((void **)&B.host_scal, (size_t)2 * K * kScalWords * 8, hipHostMallocDefault), "hipHostMalloc");
+    if (!B.host_scal) B.host_scal = alloc_scal(K);
     B.K = K;
     return B;
 }
@@ -1655,7 +1665,7 @@ hpgmx_status hpgmx_mg_setup(hpgmx_handle h, const hpgmx_mg_desc *mg)
             nx /= 2; ny /= 2; nz /= 2;
         }
         ensure_common(h);
-        if (!h->host_scal) hip_check(hipHostMalloc((void **)&h->host_scal, 256, hipHostMallocDefault), "hipHostMalloc");
+        if (!h->host_scal) h->host_scal = alloc_scal(1);
         int over = 0;
         hip_check(hipMemcpyAsync(&over, overflow, sizeof(int), hipMemcpyDeviceToHost, h->stream), "hipMemcpyAsync");
         hip_check(hipStreamSynchronize(h->stream), "hipStreamSynchronize");

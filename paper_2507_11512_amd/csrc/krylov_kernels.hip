@@ -36,6 +36,10 @@ int red_blocks(i64 N)
 // nowhere), by the thread that wrote it.  A copy after each step was a
 // launch of its own (2-4 us) and, for a batch, a strided transfer that cost
 // 85 us a step: a 3 x 40x48x56 batch took 12.1 ms with it, 7.9 without.
+// The host reads the block once an event recorded behind this kernel has
+// completed; that event has no system-scope release of its own, so the
+// thread ends with one: every store has reached the memory that the host
+// reads before the kernel, and with it the event, can complete.
 __device__ __forceinline__ void scalars_to_host(const Ctrl *c, double *host)
 {
     if (!host) return;
@@ -45,6 +49,7 @@ __device__ __forceinline__ void scalars_to_host(const Ctrl *c, double *host)
     for (int i = 0; i < 6; ++i) __hip_atomic_store(host + i, v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __hip_atomic_store(reinterpret_cast<unsigned long long *>(host) + 6, flags, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
 }
 
 // Givens update of Hessenberg column k (0-based) in FP64, by one workgroup:
