@@ -39,7 +39,6 @@ struct Level {
     // [1] float, [2] __half, [3] bf16
     void *r[4] = {nullptr, nullptr, nullptr, nullptr};
     void *z[4] = {nullptr, nullptr, nullptr, nullptr};
-    void *z2[4] = {nullptr, nullptr, nullptr, nullptr};  // second z of the tiled sweeps, where they are used
 };
 
 // How the SpMV after a V-cycle shares its work with the V-cycle's last
@@ -57,7 +56,7 @@ struct Krylov {
     void *z = nullptr;  // V-cycle output (multigrid vector type), SpMV input
     void *u = nullptr;  // end-of-cycle Q y (Krylov type)
     void *r0 = nullptr; // 16-bit hierarchy: the scaled V-cycle input
-    void *part = nullptr;  // partial SpMV sums of the last sweep (Krylov type, N entries)
+    void *part = nullptr;  // partial SpMV sums of the last sweep (Krylov type, N entries); the V-cycle's spare vector
 };
 
 // Index of the multigrid vector type: 0 double, 1 float, 2 __half, 3 bf16.
@@ -84,7 +83,6 @@ struct Batch {
     double *partials = nullptr;                              // kMaxBasis * K columns
     double *host_scal = nullptr;                             // pinned scalar blocks
     void *lr[2][kMaxLevels] = {}, *lz[2][kMaxLevels] = {};  // levels >= 1, [0] double, [1] float
-    void *lz2[2][kMaxLevels] = {};                          // second z of the tiled sweeps, where they are used
     Krylov kry[2];                                           // per vector type
     void *tmp[2][3] = {};                                    // ABI staging and autotuning
     BatchTune tune[4];                                       // per matrix precision (Prec)
@@ -171,9 +169,6 @@ struct hpgmx_ctx {
         owned.push_back(p);
         return p;
     }
-
-    // Whether the bound workspace, if there is one, still has room for `bytes`.
-    bool fits(size_t bytes) const { return !ws_base || ws_used + round_up(bytes) <= ws_size; }
 
     // profiling scopes around single launches
     void prof_begin(int kernel, int level)
@@ -344,12 +339,9 @@ void ensure_level_vectors(hpgmx_ctx *c, Prec p)
     const int vt = vt_of(p);
     for (size_t l = 1; l < c->lv.size(); ++l) {
         Level &L = c->lv[l];
-        if (!L.r[vt]) {
-            L.r[vt] = gathered_vector(c, L.A.g.N, p);
-            L.z[vt] = gathered_vector(c, L.A.g.N, p);
-        }
-        const size_t b = (size_t)L.A.g.N * vec_bytes(p);
-        if (!L.z2[vt] && tiled_size(c->layout, L.A.g.N, 1, p) && c->fits(b)) L.z2[vt] = c->dalloc(b);
+        if (L.r[vt]) continue;
+        L.r[vt] = gathered_vector(c, L.A.g.N, p);
+        L.z[vt] = gathered_vector(c, L.A.g.N, p);
     }
 }
 
@@ -438,10 +430,6 @@ size_t plan_bytes(const hpgmx_problem_desc &pd, const hpgmx_mg_desc &mg, int m, 
                 const bool want = vt == 0 ? (mask & 1u) != 0 : vt == 1 ? (mask & 0xEu) != 0
                                                                        : (mask >> (vt + 2)) & 1u;
                 if (want) { add((N + 1) * vt_bytes[vt]); add((N + 1) * vt_bytes[vt]); }
-                bool second = false;  // the tiled sweeps' second z
-                for (int p = 0; p < kNumPrec; ++p)
-                    second = second || (((mask >> p) & 1u) && vt_of((Prec)p) == vt && tiled_size(lay, (i64)N, 1, (Prec)p));
-                if (second) add(N * vt_bytes[vt]);
             }
         nx /= 2; ny /= 2; nz /= 2;
     }
@@ -578,45 +566,49 @@ void presmooth_restrict(hpgmx_ctx *c, int l, Prec p, int kind, int nsweeps, cons
         launch_restrict(c->lv[l].A, gc, p, r, z, rc, c->stream);
 }
 
-// Whether a V-cycle runs level l in tiles, with z2 as its second vector.
-bool tiled_level(const hpgmx_ctx *c, int l, Prec p, int K, const void *z2)
+// Whether a V-cycle runs level l in tiles.
+bool tiled_level(const hpgmx_ctx *c, int l, Prec p, int K)
 {
     const hpgmx_mg_desc &mg = c->mg;
     const bool smooths = l == mg.levels - 1 ? mg.coarsest_sweeps > 0 : mg.pre_sweeps > 0 && mg.post_sweeps > 0;
-    return z2 && smooths && tiled(c, l, p, K);
+    return smooths && tiled(c, l, p, K);
 }
 
-// A V-cycle level in tiles; coarse(rc, zc) runs the coarser levels.
+// A V-cycle level in tiles, with `spare` as the second vector of its sweeps;
+// coarse(spare) runs the coarser levels, with the one of z and spare that
+// holds nothing between the pre- and the post-sweeps.
 template <typename F>
-void tiled_vcycle(hpgmx_ctx *c, int l, Prec p, int K, const void *r, void *z, void *z2, void *rc, const void *zc,
+void tiled_vcycle(hpgmx_ctx *c, int l, Prec p, int K, const void *r, void *z, void *spare, void *rc, const void *zc,
                   F &&coarse)
 {
     const hpgmx_mg_desc &mg = c->mg;
     if (l == mg.levels - 1) {
-        tiled_sweeps(c, l, p, K, mg.sweep, mg.coarsest_sweeps, r, nullptr, z, z2, nullptr, nullptr);
+        tiled_sweeps(c, l, p, K, mg.sweep, mg.coarsest_sweeps, r, nullptr, z, spare, nullptr, nullptr);
         return;
     }
     // the pre-sweeps end in the vector that the post-sweeps, which end in z, start from
-    void *x = half_sweeps(mg.sweep, mg.post_sweeps) & 1 ? z2 : z;
-    tiled_sweeps(c, l, p, K, mg.sweep, mg.pre_sweeps, r, nullptr, x, x == z ? z2 : z, nullptr, rc);
-    coarse();
-    tiled_sweeps(c, l, p, K, mg.sweep, mg.post_sweeps, r, x, z, z2, zc, nullptr);
+    void *x = half_sweeps(mg.sweep, mg.post_sweeps) & 1 ? spare : z, *other = x == z ? spare : z;
+    tiled_sweeps(c, l, p, K, mg.sweep, mg.pre_sweeps, r, nullptr, x, other, nullptr, rc);
+    coarse(other);
+    tiled_sweeps(c, l, p, K, mg.sweep, mg.post_sweeps, r, x, z, spare, zc, nullptr);
 }
 
 // z = M^{-1} r on level l (z is overwritten; the cycle starts from zero).
 // With out.w (level 0 only, see fused_spmv_colour) the last colour launch
-// also writes its rows of w = A z.  z2: a second vector of z's size on level
-// 0 (the other levels have their own) for the tiled sweeps, which write no
-// SpMV rows.
-void vcycle(hpgmx_ctx *c, int l, Prec p, const void *r, void *z, SpmvOut out = {}, void *z2 = nullptr)
+// also writes its rows of w = A z (the tiled sweeps write none).  spare: a
+// vector of at least as many elements as the level has rows, whose contents
+// the cycle may overwrite: the second vector of the tiled sweeps, which thus
+// need no memory of their own.  Where the level's own sweeps don't use it
+// before the post-sweeps (out.part may be it), the coarser levels have it.
+void vcycle(hpgmx_ctx *c, int l, Prec p, const void *r, void *z, void *spare, SpmvOut out = {})
 {
     const hpgmx_mg_desc &mg = c->mg;
     const int vt = vt_of(p);
-    if (l > 0) z2 = c->lv[l].z2[vt];
-    if (!out.w && !out.part && tiled_level(c, l, p, 1, z2)) {
+    if (!out.w && !out.part && tiled_level(c, l, p, 1)) {
         const bool leaf = l == mg.levels - 1;
-        tiled_vcycle(c, l, p, 1, r, z, z2, leaf ? nullptr : c->lv[l + 1].r[vt], leaf ? nullptr : c->lv[l + 1].z[vt],
-                     [&]() { vcycle(c, l + 1, p, c->lv[l + 1].r[vt], c->lv[l + 1].z[vt]); });
+        tiled_vcycle(c, l, p, 1, r, z, spare, leaf ? nullptr : c->lv[l + 1].r[vt],
+                     leaf ? nullptr : c->lv[l + 1].z[vt],
+                     [&](void *sp) { vcycle(c, l + 1, p, c->lv[l + 1].r[vt], c->lv[l + 1].z[vt], sp); });
         return;
     }
     if (l == mg.levels - 1) {
@@ -625,7 +617,7 @@ void vcycle(hpgmx_ctx *c, int l, Prec p, const void *r, void *z, SpmvOut out = {
     }
     Level &C = c->lv[l + 1];
     presmooth_restrict(c, l, p, mg.sweep, mg.pre_sweeps, r, z, C.r[vt]);
-    vcycle(c, l + 1, p, C.r[vt], C.z[vt]);
+    vcycle(c, l + 1, p, C.r[vt], C.z[vt], spare);
     {
         ProfScope ps(c, HPGMX_K_PROLONG, l);
         launch_prolong(c->lv[l].A.g, C.A.g, p, C.z[vt], z, c->stream);
@@ -831,7 +823,7 @@ hpgmx_status solve(hpgmx_ctx *c, const double *b, double *x, const hpgmx_solve_d
                     // (tiled sweeps leave all of it to the SpMV: the same bits)
                     const int fc = fused_spmv_colour(c);
                     int sm = fc < 0 ? kSpmvPlain : c->spmv_mode;
-                    if (tiled_level(c, 0, p, 1, K.part))
+                    if (tiled_level(c, 0, p, 1))
                         sm = sm == kSpmvLast ? kSpmvPlain : sm == kSpmvSplit ? kSpmvSplitSeparate : sm;
                     SpmvOut out{};
                     if (sm == kSpmvLast || sm == kSpmvSplit) { out.w = col(k + 1); out.scale = spmv_scale(p, c->ctrl, k); }
@@ -841,9 +833,9 @@ hpgmx_status solve(hpgmx_ctx *c, const double *b, double *x, const hpgmx_solve_d
                             ProfScope ps(c, HPGMX_K_CAST, 0);
                             launch_cast_mg(N, p, (const float *)col(k), c->ctrl, false, k, K.r0, c->stream);
                         }
-                        vcycle(c, 0, p, K.r0, K.z, out, K.part);
+                        vcycle(c, 0, p, K.r0, K.z, K.part, out);
                     } else {
-                        vcycle(c, 0, p, col(k), K.z, out, K.part);
+                        vcycle(c, 0, p, col(k), K.z, K.part, out);
                     }
                     {
                         ProfScope ps(c, HPGMX_K_SPMV, 0);
@@ -905,9 +897,9 @@ hpgmx_status solve(hpgmx_ctx *c, const double *b, double *x, const hpgmx_solve_d
                     ProfScope ps(c, HPGMX_K_CAST, 0);
                     launch_cast_mg(N, p, (const float *)K.u, c->ctrl, true, kk, K.r0, c->stream);
                 }
-                vcycle(c, 0, p, K.r0, K.z, {}, K.part);
+                vcycle(c, 0, p, K.r0, K.z, K.part);
             } else {
-                vcycle(c, 0, p, K.u, K.z, {}, K.part);
+                vcycle(c, 0, p, K.u, K.z, K.part);
             }
             {
                 ProfScope ps(c, HPGMX_K_UPDATE, 0);
@@ -968,12 +960,9 @@ void ensure_batch_prec(hpgmx_ctx *c, Batch &B, Prec p, int m)
     ensure_prec(c, p);
     ensure_prec(c, P64);
     for (size_t l = 1; l < c->lv.size(); ++l) {
-        if (!B.lr[vt][l]) {
-            B.lr[vt][l] = gathered_batch(c, c->lv[l].A.g.N, K, p);
-            B.lz[vt][l] = gathered_batch(c, c->lv[l].A.g.N, K, p);
-        }
-        const size_t b = (size_t)c->lv[l].A.g.N * K * vec_bytes(p);
-        if (!B.lz2[vt][l] && tiled_size(c->layout, c->lv[l].A.g.N, K, p) && c->fits(b)) B.lz2[vt][l] = c->dalloc(b);
+        if (B.lr[vt][l]) continue;
+        B.lr[vt][l] = gathered_batch(c, c->lv[l].A.g.N, K, p);
+        B.lz[vt][l] = gathered_batch(c, c->lv[l].A.g.N, K, p);
     }
     if (m <= 0) return;
     const i64 N0 = c->lv[0].A.g.N;
@@ -1075,21 +1064,20 @@ bool btiled(const hpgmx_ctx *c, const Batch &B, int l, Prec p)
     const BatchTune &t = B.tune[p];
     return tiled(c, l, p, B.K) && !(t.given && (t.R[HPGMX_BK_GS][l] || t.R[HPGMX_BK_GS_ZERO][l]));
 }
-bool btiled_level(const hpgmx_ctx *c, const Batch &B, int l, Prec p, const void *z2)
+bool btiled_level(const hpgmx_ctx *c, const Batch &B, int l, Prec p)
 {
-    return tiled_level(c, l, p, B.K, z2) && btiled(c, B, l, p);
+    return tiled_level(c, l, p, B.K) && btiled(c, B, l, p);
 }
 
-// The V-cycle of vcycle() for K right-hand sides at once (out, z2: as vcycle()).
-void bvcycle(hpgmx_ctx *c, Batch &B, int l, Prec p, const void *r, void *z, BSpmvOut out = {}, void *z2 = nullptr)
+// The V-cycle of vcycle() for K right-hand sides at once (spare, out: as vcycle()).
+void bvcycle(hpgmx_ctx *c, Batch &B, int l, Prec p, const void *r, void *z, void *spare, BSpmvOut out = {})
 {
     const hpgmx_mg_desc &mg = c->mg;
     const int vt = vt_of(p);
-    if (l > 0) z2 = B.lz2[vt][l];
-    if (!out.y && !out.part && btiled_level(c, B, l, p, z2)) {
+    if (!out.y && !out.part && btiled_level(c, B, l, p)) {
         const bool leaf = l == mg.levels - 1;
-        tiled_vcycle(c, l, p, B.K, r, z, z2, leaf ? nullptr : B.lr[vt][l + 1], leaf ? nullptr : B.lz[vt][l + 1],
-                     [&]() { bvcycle(c, B, l + 1, p, B.lr[vt][l + 1], B.lz[vt][l + 1]); });
+        tiled_vcycle(c, l, p, B.K, r, z, spare, leaf ? nullptr : B.lr[vt][l + 1], leaf ? nullptr : B.lz[vt][l + 1],
+                     [&](void *sp) { bvcycle(c, B, l + 1, p, B.lr[vt][l + 1], B.lz[vt][l + 1], sp); });
         return;
     }
     if (l == mg.levels - 1) {
@@ -1098,7 +1086,7 @@ void bvcycle(hpgmx_ctx *c, Batch &B, int l, Prec p, const void *r, void *z, BSpm
     }
     const Geom &gc = c->lv[l + 1].A.g;
     bpresmooth_restrict(c, B, l, p, mg.sweep, mg.pre_sweeps, r, z, B.lr[vt][l + 1]);
-    bvcycle(c, B, l + 1, p, B.lr[vt][l + 1], B.lz[vt][l + 1]);
+    bvcycle(c, B, l + 1, p, B.lr[vt][l + 1], B.lz[vt][l + 1], spare);
     {
         ProfScope ps(c, HPGMX_K_PROLONG, l);
         launch_bprolong(c->lv[l].A.g, gc, p, B.K, B.lz[vt][l + 1], z, c->stream);
@@ -1280,10 +1268,10 @@ hpgmx_status bsolve(hpgmx_ctx *c, int nrhs, const double *Bn, double *Xn, const 
                     const int fc = fused_spmv_colour(c);
                     int sm = fc < 0 || (p != P32 && p != P64) || c->spmv_mode == kSpmvLast ? kSpmvPlain
                                                                                             : c->spmv_mode;
-                    if (sm == kSpmvSplit && btiled_level(c, B, 0, p, Kr.part)) sm = kSpmvSplitSeparate;
+                    if (sm == kSpmvSplit && btiled_level(c, B, 0, p)) sm = kSpmvSplitSeparate;
                     BSpmvOut out{};
                     if (sm == kSpmvSplit) { out.y = col(k + 1); out.ctrl = B.ctrl; out.k = k; out.part = Kr.part; }
-                    bvcycle(c, B, 0, p, col(k), Kr.z, out, Kr.part);
+                    bvcycle(c, B, 0, p, col(k), Kr.z, Kr.part, out);
                     {
                         ProfScope ps(c, HPGMX_K_SPMV, 0);
                         const int Rs = tile_r(c, B, p, HPGMX_BK_SPMV, 0);
@@ -1361,7 +1349,7 @@ hpgmx_status bsolve(hpgmx_ctx *c, int nrhs, const double *Bn, double *Xn, const 
                 ProfScope ps(c, HPGMX_K_GEMV, 0);
                 launch_gemv(M, K, p, Kr.Q, ldq, kmax, B.ctrl, Kr.u, c->stream);
             }
-            bvcycle(c, B, 0, p, Kr.u, Kr.z, {}, Kr.part);
+            bvcycle(c, B, 0, p, Kr.u, Kr.z, Kr.part);
             {
                 ProfScope ps(c, HPGMX_K_UPDATE, 0);
                 launch_update(M, p, Kr.z, B.x, c->stream);
@@ -1411,10 +1399,6 @@ size_t plan_batch_bytes(const hpgmx_problem_desc &pd, const hpgmx_mg_desc &mg, i
             const size_t N = (size_t)nx * ny * nz;
             add((N + 1) * K * vb);
             add((N + 1) * K * vb);
-            bool second = false;  // the tiled sweeps' second z
-            for (int p = 0; p < 4; ++p)
-                second = second || (((mask >> p) & 1u) && vt_of((Prec)p) == vt && tiled_size(lay, (i64)N, K, (Prec)p));
-            if (second) add(N * K * vb);
             nx /= 2; ny /= 2; nz /= 2;
         }
         add((size_t)krylov_ldq((i64)(N0 * K), lay.ldq_pad) * (m + 1) * vb);
@@ -1759,7 +1743,7 @@ hpgmx_status hpgmx_vcycle(hpgmx_handle h, int dtype, const void *r, void *z)
         const Prec pv = vprec(p);
         launch_nat2int(A.g, pv, r, pv, h->tmp[vt][0], h->stream,
                        entry(h->tmp[vt][1], A.g.N, pv));
-        vcycle(h, 0, p, h->tmp[vt][0], h->tmp[vt][1], {}, h->tmp[vt][2]);
+        vcycle(h, 0, p, h->tmp[vt][0], h->tmp[vt][1], h->tmp[vt][2]);
         launch_int2nat(A.g, pv, h->tmp[vt][1], pv, z, h->stream);
         return HPGMX_OK;
     });
@@ -2096,7 +2080,7 @@ hpgmx_status hpgmx_vcycle_batched(hpgmx_handle h, int dtype, int nrhs, const voi
         const Matrix &A = h->lv[0].A;
         launch_bnat2int(A.g, p, p, K, nrhs, R, B.tmp[vt][0], h->stream,
                         entry(B.tmp[vt][1], A.g.N * K, p));
-        bvcycle(h, B, 0, p, B.tmp[vt][0], B.tmp[vt][1], {}, B.tmp[vt][2]);
+        bvcycle(h, B, 0, p, B.tmp[vt][0], B.tmp[vt][1], B.tmp[vt][2]);
         launch_bint2nat(A.g, p, p, K, nrhs, B.tmp[vt][1], Z, h->stream);
         return HPGMX_OK;
     });

@@ -169,3 +169,42 @@ def test_solve_in_bound_workspace(hp, bound):
     assert all(np.array_equal(out[0], o) for o in out[1:])
     ref = inputs.uniform(dims, 44)
     assert np.linalg.norm(out[0] - ref) <= 1e-8 * np.linalg.norm(ref)
+
+
+def test_workspace_without_second_vectors(hp):
+    """The tiled sweeps take no memory of their own: a workspace that holds what the colour launches need holds every
+    call, in the order that takes the single-precision vectors first, and gives the iterates of owned memory."""
+    import torch
+    dims, mask = (48, 40, 32), 0x3F
+    size = []
+    for lay in ({}, {"pair_rows": 0}):
+        h = hp.setup_problem(*dims, beta=0.3)
+        hp.set_layout(h, **lay)
+        size.append(hp.workspace_bytes(h, levels=3, restart=30, dtype_mask=mask) +
+                    hp.workspace_bytes_batched(h, 4, levels=3, restart=30, dtype_mask=0xF))
+        hp.destroy(h)
+    assert size[0] == size[1]
+    ws = torch.empty(size[1], dtype=torch.uint8, device="cuda")
+    Ps = [hp.Problem(dims, beta=0.3, levels=3, sweep="symmetric", workspace=w) for w in (None, ws)]
+    try:
+        out = [[], []]
+        for P, o in zip(Ps, out):
+            b = P.rhs_from_x(vec(dims, 44, 0))
+            B = torch.stack([b, 2 * b, b.flip(0)])
+            for dtype in (1, 0, 4, 5):
+                z = torch.zeros_like(vec(dims, 45, dtype))
+                hp.vcycle(P.h, dtype, vec(dims, 45, dtype), z)
+                o.append(z)
+            for dtype in (1, 0):
+                R = B.to(getattr(torch, VEC.get(dtype, "float32")))
+                Z = torch.zeros_like(R)
+                hp.vcycle_batched(P.h, dtype, R, Z)
+                o.append(Z)
+            for precision in ("mxp", "fp64", "fp16", "bf16", "fp16-mg", "bf16-mg"):
+                o.append(P.solve(b, tol=1e-9, precision=precision)[0])
+            for precision in ("mxp", "fp64", "fp16", "bf16"):
+                o.append(P.solve_batched(B, tol=1e-9, precision=precision)[0])
+        assert all(torch.equal(a, c) for a, c in zip(*out))
+    finally:
+        for P in Ps:
+            P.close()
