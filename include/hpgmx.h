@@ -365,7 +365,12 @@ hpgmx_status hpgmx_profile_get(hpgmx_handle h, int kernel, int level, double *to
  * device and keeps the fastest; without it the library uses a fixed rule
  * (R = K on levels with at least 2^22 / K rows, R = 1 below).  The choice
  * never changes results: per (row, right-hand side) the arithmetic is the
- * same for every R. */
+ * same for every R.  The table shapes launches, it does not choose among
+ * them: the half sweeps that run as one launch (see pair_rows in
+ * hpgmx_set_layout), and the split SpMV of small batches after them, have
+ * shapes of their own whatever R says; the GS kinds' times are those of the
+ * colour launches, on such levels too (hpgmx_presmooth_restrict_batched and
+ * layouts without those half sweeps launch these). */
 #define HPGMX_BK_SPMV 0      /* batched SpMV                                  */
 #define HPGMX_BK_GS 1        /* one colour of a batched GS sweep              */
 #define HPGMX_BK_GS_ZERO 2   /* one colour of a batched sweep from zero       */

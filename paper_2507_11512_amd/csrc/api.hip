@@ -70,7 +70,6 @@ struct BatchTune {
     int R[HPGMX_BK_COUNT][kMaxLevels] = {};
     double ms[HPGMX_BK_COUNT][kMaxLevels] = {};
     bool set = false;
-    bool given = false;  // by hpgmx_batch_set_tuning: these tiles are launched
 };
 
 // State of batched solves with K interleaved right-hand sides.  Vectors are
@@ -994,7 +993,9 @@ void ensure_batch_tmp(hpgmx_ctx *c, Batch &B, int vt)
 
 // R of a batched kernel: the adopted table, else the fixed rule (every lane
 // takes the whole row on large levels, one right-hand side per lane on
-// small ones, where parallelism is scarce).
+// small ones, where parallelism is scarce).  It shapes the kernels that take
+// an R where these run; which sweeps run in tiles is no part of the table
+// (tiled()), so that a table read back and set again changes nothing.
 int tile_r(const hpgmx_ctx *c, const Batch &B, Prec p, int kind, int l)
 {
     const int R = B.tune[p].R[kind][l];
@@ -1057,24 +1058,12 @@ void bpresmooth_restrict(hpgmx_ctx *c, Batch &B, int l, Prec p, int kind, int ns
         launch_brestrict(c->lv[l].A, gc, p, B.K, R, r, z, rc, c->stream);
 }
 
-// tiled() for a batch: a table of tile shapes set by the caller asks for the
-// colour launches it describes.
-bool btiled(const hpgmx_ctx *c, const Batch &B, int l, Prec p)
-{
-    const BatchTune &t = B.tune[p];
-    return tiled(c, l, p, B.K) && !(t.given && (t.R[HPGMX_BK_GS][l] || t.R[HPGMX_BK_GS_ZERO][l]));
-}
-bool btiled_level(const hpgmx_ctx *c, const Batch &B, int l, Prec p)
-{
-    return tiled_level(c, l, p, B.K) && btiled(c, B, l, p);
-}
-
 // The V-cycle of vcycle() for K right-hand sides at once (spare, out: as vcycle()).
 void bvcycle(hpgmx_ctx *c, Batch &B, int l, Prec p, const void *r, void *z, void *spare, BSpmvOut out = {})
 {
     const hpgmx_mg_desc &mg = c->mg;
     const int vt = vt_of(p);
-    if (!out.y && !out.part && btiled_level(c, B, l, p)) {
+    if (!out.y && !out.part && tiled_level(c, l, p, B.K)) {
         const bool leaf = l == mg.levels - 1;
         tiled_vcycle(c, l, p, B.K, r, z, spare, leaf ? nullptr : B.lr[vt][l + 1], leaf ? nullptr : B.lz[vt][l + 1],
                      [&](void *sp) { bvcycle(c, B, l + 1, p, B.lr[vt][l + 1], B.lz[vt][l + 1], sp); });
@@ -1268,7 +1257,7 @@ hpgmx_status bsolve(hpgmx_ctx *c, int nrhs, const double *Bn, double *Xn, const 
                     const int fc = fused_spmv_colour(c);
                     int sm = fc < 0 || (p != P32 && p != P64) || c->spmv_mode == kSpmvLast ? kSpmvPlain
                                                                                             : c->spmv_mode;
-                    if (sm == kSpmvSplit && btiled_level(c, B, 0, p)) sm = kSpmvSplitSeparate;
+                    if (sm == kSpmvSplit && tiled_level(c, 0, p, K)) sm = kSpmvSplitSeparate;
                     BSpmvOut out{};
                     if (sm == kSpmvSplit) { out.y = col(k + 1); out.ctrl = B.ctrl; out.k = k; out.part = Kr.part; }
                     bvcycle(c, B, 0, p, col(k), Kr.z, Kr.part, out);
@@ -1957,7 +1946,7 @@ hpgmx_status hpgmx_batch_set_tuning(hpgmx_handle h, int nrhs, int dtype, const h
                 T.R[k][l] = in->rhs_per_lane[k][l];
                 T.ms[k][l] = in->ms[k][l];
             }
-        T.set = T.given = true;
+        T.set = true;
         B.tune[p] = T;
         h->drop_graphs();
         return HPGMX_OK;
@@ -2022,7 +2011,7 @@ hpgmx_status hpgmx_smooth_batched(hpgmx_handle h, int level, int dtype, int swee
                         entry(B.tmp[vt][1], A.g.N * K, p));
         if (!zero_guess) launch_bnat2int(A.g, p, p, K, nrhs, Z, B.tmp[vt][1], h->stream);
         void *out = B.tmp[vt][1];
-        if (btiled(h, B, level, p)) {
+        if (tiled(h, level, p, K)) {
             void *other = B.tmp[vt][2];
             if (half_sweeps(sweep, 1) & 1) std::swap(out, other);
             tiled_sweeps(h, level, p, K, sweep, 1, B.tmp[vt][0], zero_guess ? nullptr : B.tmp[vt][1], out, other,

@@ -29,6 +29,22 @@ def pair(hp, dims, **kw):
     return [hp.Problem(dims, beta=0.3, layout=lay, **kw) for lay in (None, {"pair_rows": 0})]
 
 
+def launches(hp, P, call):
+    """Number of launches `call` enqueues on P's stream (which must not be the default one), by capturing it."""
+    import ctypes as C
+    import torch
+    stream, graph, n = C.c_void_p(P.stream.cuda_stream), C.c_void_p(), C.c_size_t()
+    call()  # what a first call allocates and works out
+    torch.cuda.synchronize()
+    assert hp.lib.hipStreamBeginCapture(stream, 1) == 0  # 1: thread-local
+    try:
+        call()
+    finally:
+        assert hp.lib.hipStreamEndCapture(stream, C.byref(graph)) == 0
+    assert hp.lib.hipGraphGetNodes(graph, None, C.byref(n)) == 0 and hp.lib.hipGraphDestroy(graph) == 0
+    return n.value
+
+
 # tile edges: one cell, fewer cells than a tile, odd extents in each direction, several tiles with a remainder, tiles
 # of several row chunks, the largest level (2^22 rows; in FP64 beyond its largest), long and short x-lines
 DIMS = [(2, 2, 2), (3, 5, 4), (13, 9, 7), (2, 34, 3), (64, 3, 2), (37, 26, 51), (50, 38, 26), (100, 102, 102), (131, 70, 99),
@@ -208,3 +224,58 @@ def test_workspace_without_second_vectors(hp):
     finally:
         for P in Ps:
             P.close()
+
+
+def test_tuning_table_keeps_the_dispatch(hp):
+    """A table of tile shapes that is read back and set on another handle, or set by hand, leaves the sweeps in tiles:
+    as many launches as without a table, fewer than a launch per colour."""
+    import torch
+    dims, nrhs = (32, 32, 32), 4
+    r = torch.stack([vec(dims, 80 + j, 1) for j in range(nrhs)])
+    Ps = [hp.Problem(dims, levels=3, stream=torch.cuda.Stream(), layout=lay) for lay in (None, None, {"pair_rows": 0})]
+    try:
+        def count(P):
+            z = torch.zeros_like(r)
+            return (launches(hp, P, lambda: hp.vcycle_batched(P.h, 1, r, z)),
+                    launches(hp, P, lambda: hp.smooth_batched(P.h, 0, 1, hp.GS_FORWARD, r, z)))
+        plain, colours = count(Ps[0]), count(Ps[2])
+        assert plain[0] < colours[0] - 20 and plain[1] == colours[1] - 7
+        table = hp.batch_autotune(Ps[0].h, nrhs, 1)["rhs_per_lane"]
+        assert count(Ps[0]) == plain
+        hp.batch_set_tuning(Ps[1].h, nrhs, 1, table)
+        assert hp.batch_get_tuning(Ps[1].h, nrhs, 1)["rhs_per_lane"] == table and count(Ps[1]) == plain
+        hp.batch_set_tuning(Ps[1].h, nrhs, 1, 1)
+        assert count(Ps[1]) == plain
+    finally:
+        for P in Ps:
+            P.close()
+
+
+@pytest.mark.parametrize("dims,levels", [((16, 16, 16), 3), ((24, 20, 16), 3), ((14, 18, 10), 2)])
+@pytest.mark.parametrize("nrhs", [2, 3, 8])
+@pytest.mark.parametrize("dtype", [0, 1, 3])
+def test_colour_launches_every_tile_shape(hp, dims, levels, nrhs, dtype):
+    """The batched colour launches in every tile shape against the tiled sweeps."""
+    import torch
+    K = 2 if nrhs <= 2 else 4 if nrhs <= 4 else 8
+    for sweep in ("forward", "backward", "symmetric"):
+        P, Q = pair(hp, dims, levels=levels, sweep=sweep)
+        try:
+            r = torch.stack([vec(dims, 90 + j, dtype) for j in range(nrhs)])
+            code = {"forward": hp.GS_FORWARD, "backward": hp.GS_BACKWARD, "symmetric": hp.GS_SYMMETRIC}[sweep]
+
+            def results(H):
+                out = [torch.full_like(r, float("nan")), torch.full_like(r, float("nan")), r.clone()]
+                hp.vcycle_batched(H.h, dtype, r, out[0])
+                hp.smooth_batched(H.h, 0, dtype, code, r, out[1], zero_guess=True)
+                hp.smooth_batched(H.h, 0, dtype, code, r, out[2])
+                return out
+            ref = results(P)
+            for R in (1, 2, 4, 8):
+                if R > K:
+                    continue
+                hp.batch_set_tuning(Q.h, nrhs, dtype, R)
+                assert all(torch.equal(a, b) for a, b in zip(results(Q), ref)), (sweep, R)
+        finally:
+            P.close()
+            Q.close()
