@@ -201,7 +201,8 @@ hpgmx_status hpgmx_set_column_format(hpgmx_handle h, int format);
  *                  2^17).  With the default, and without profiling, levels
  *                  of up to 2^22 rows (3 * 2^19 in FP64; batches 7 * 2^18
  *                  rows times right-hand sides, 9 * 2^17 in FP64) run each
- *                  half sweep as one launch instead.
+ *                  half sweep as one launch instead, unless their x-lines
+ *                  are so long that this is slower.
  *   spmv_in_sweep  how the solver's SpMV w = A z after each V-cycle shares
  *                  work with the V-cycle's last level-0 sweep.  0: one SpMV
  *                  over all rows.  1: the sweep's last colour launch (whose

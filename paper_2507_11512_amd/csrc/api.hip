@@ -307,30 +307,13 @@ void *gathered_vector(hpgmx_ctx *c, i64 N, Prec p)
 // that fills one clears the entry of the level used.
 void *entry(void *v, i64 N, Prec p) { return (char *)v + (size_t)N * vec_bytes(p); }
 
-// Levels whose half-sweeps run as one launch each (launch_sweep), by their
-// rows times right-hand sides.  Small ones gain the launches' latency; larger
-// ones still gain, because a tile's matrix entries are its values alone and
-// its neighbours come from LDS, until the halo rows cost more.  A 30-step
-// cycle with 4 levels, colour launches and tiles on level 0 (times in us):
-// FP32 64^3 (3 levels) 5467 and 4205, 112^3 9966 and 8298, 128^3 12039 and
-// 10357, 160^3 19852 and 18595; bfloat16 160^3 17470 and 16770; FP64 96^3
-// 10698 and 9108, 112^3 14003 and 13589, but 128^3 17882 and 18273.  Batches:
-// FP32 2 x 96^3 8957 and 7434, 4 x 80^3 8782 and 8677, but 4 x 96^3 12312
-// and 14287; binary16 4 x 64^3 6335 and 5540, but 4 x 80^3 8699 and 8791;
-// FP64 2 x 80^3 9388 and 8639, but 2 x 96^3 13636 and 13944.  The lines lie
-// between these.  Larger levels keep the launches per colour, which read the
-// columns as they are stored.  A handle with a pair_rows of its own gets the
-// launches it asks for, and a profiled solve the launches that are timed one
-// by one.
-bool tiled_size(const Layout &lay, i64 N, int K, Prec p)
+// Whether the half-sweeps of sweeps of `kind` on level l, in a V-cycle or by
+// themselves, run as one launch each, where that is the faster way (sweep_pays).  A handle with a pair_rows
+// of its own gets the launches it asks for, and a profiled solve the launches
+// that are timed one by one.
+bool tiled(const hpgmx_ctx *c, int l, Prec p, int K, int kind, bool cycle)
 {
-    const i64 most = K == 1 ? (p == P64 ? 3 << 19 : 1 << 22) : (p == P64 ? 9 << 17 : 7 << 18);
-    return lay.pair_rows == kDefaultPairRows && N * K <= most;
-}
-bool tiled(const hpgmx_ctx *c, int l, Prec p, int K)
-{
-    const Matrix &A = c->lv[l].A;
-    return !c->prof && tiled_size(c->layout, A.g.N, K, p) && sweep_possible(A, K, p);
+    return !c->prof && c->layout.pair_rows == kDefaultPairRows && sweep_pays(c->lv[l].A, K, p, kind, cycle);
 }
 
 void ensure_level_vectors(hpgmx_ctx *c, Prec p)
@@ -570,7 +553,7 @@ bool tiled_level(const hpgmx_ctx *c, int l, Prec p, int K)
 {
     const hpgmx_mg_desc &mg = c->mg;
     const bool smooths = l == mg.levels - 1 ? mg.coarsest_sweeps > 0 : mg.pre_sweeps > 0 && mg.post_sweeps > 0;
-    return smooths && tiled(c, l, p, K);
+    return smooths && tiled(c, l, p, K, mg.sweep, true);
 }
 
 // A V-cycle level in tiles, with `spare` as the second vector of its sweeps;
@@ -1704,7 +1687,7 @@ hpgmx_status hpgmx_smooth(hpgmx_handle h, int level, int dtype, int sweep, const
                        entry(h->tmp[vt][1], A.g.N, pv));
         if (!zero_guess) launch_nat2int(A.g, pv, z, pv, h->tmp[vt][1], h->stream);
         void *out = h->tmp[vt][1];
-        if (tiled(h, level, p, 1)) {
+        if (tiled(h, level, p, 1, sweep, false)) {
             void *other = h->tmp[vt][2];
             if (half_sweeps(sweep, 1) & 1) std::swap(out, other);
             tiled_sweeps(h, level, p, 1, sweep, 1, h->tmp[vt][0], zero_guess ? nullptr : h->tmp[vt][1], out, other,
@@ -2011,7 +1994,7 @@ hpgmx_status hpgmx_smooth_batched(hpgmx_handle h, int level, int dtype, int swee
                         entry(B.tmp[vt][1], A.g.N * K, p));
         if (!zero_guess) launch_bnat2int(A.g, p, p, K, nrhs, Z, B.tmp[vt][1], h->stream);
         void *out = B.tmp[vt][1];
-        if (tiled(h, level, p, K)) {
+        if (tiled(h, level, p, K, sweep, false)) {
             void *other = B.tmp[vt][2];
             if (half_sweeps(sweep, 1) & 1) std::swap(out, other);
             tiled_sweeps(h, level, p, K, sweep, 1, B.tmp[vt][0], zero_guess ? nullptr : B.tmp[vt][1], out, other,

@@ -325,6 +325,9 @@ bool gs_pair_possible(const Matrix &A);
 // for a sweep from zero and as launch_restrict otherwise.  skip_first: the
 // first colour is left as it is in zin.  K interleaved right-hand sides.
 bool sweep_possible(const Matrix &A, int K, Prec p);
+// Whether such launches are the faster way for sweeps of `kind` (hpgmx_sweep),
+// in a V-cycle or by themselves.
+bool sweep_pays(const Matrix &A, int K, Prec p, int kind, bool cycle);
 void launch_sweep(const Matrix &A, Prec p, int K, bool forward, bool skip_first, const void *r, const void *zin,
                   const Geom *gc, const void *zc, void *zout, void *rc, hipStream_t s);
 void launch_restrict(const Matrix &Af, const Geom &gc, Prec p, const void *r, const void *z,

@@ -20,7 +20,8 @@
 // colour's rows, which depend on no z, are loaded while the current colour
 // is relaxed, the neighbours come from LDS, and a colour takes 0.6-0.8 us
 // (the issue of its instructions: finding the row, 26 loads, 26 LDS reads
-// and 26 dependent FMAs).  The price is the halo (1.5 to 4 times the rows).
+// and 26 dependent FMAs).  The price is the halo: 1.3 to 3 times the rows on
+// levels near cubes, up to 6 times where a line fills the LDS (sweep_pays).
 // Measured, FP32 forward, the eight launches with their gaps against this
 // one: 64^3 level 45 -> 12 us from zero with the restriction, 13.6 us with
 // the prolongation; 32^3 36 -> 10; 16^3 27 -> 8.  Solves of 16^3
@@ -494,12 +495,15 @@ i64 sweep_lanes(const SweepArgs &P, int q, int n, int m, int L)
 
 // The tile whose workgroups, taken one per CU, have the least to work through
 // one after the other: row chunks, which take a sixth less time where the
-// waves can split (k_sweep); of equal ones the smallest.  Returns the LDS
-// bytes of a workgroup.
-size_t choose_tile(const Geom &g, const SweepArgs &P, int K, int L, int threads, size_t vb, int &n, int &m)
+// waves can split (k_sweep); of equal ones the smallest.
+struct Tile {
+    int n = 1, m = 1;
+    size_t lds = 0;  // bytes of a workgroup (0: no tile fits)
+    i64 cost = 0;    // sixths of a row chunk
+};
+Tile choose_tile(const Geom &g, const SweepArgs &P, int K, int L, int threads, size_t vb)
 {
-    i64 best = -1;
-    size_t lds = 0;
+    Tile t;
     for (int mm = 1; mm <= 8; ++mm)
         for (int nn = 1; nn <= 8; ++nn) {
             const i64 cells = 1 + (i64)8 * P.sx * (P.pj - 1 + nn) * (P.pk - 1 + mm);
@@ -512,9 +516,9 @@ size_t choose_tile(const Geom &g, const SweepArgs &P, int K, int L, int threads,
                 most = std::max(most, lanes);
             }
             const i64 cost = (sweep_tiles(g, nn, mm) + kCus - 1) / kCus * items * (most <= threads / 2 ? 5 : 6);
-            if (best < 0 || cost < best) { best = cost; n = nn; m = mm; lds = b; }
+            if (t.lds == 0 || cost < t.cost) t = Tile{nn, mm, b, cost};
         }
-    return lds;
+    return t;
 }
 
 template <typename V, typename S, int K, bool SPLIT>
@@ -542,7 +546,7 @@ struct SweepPlan {
 };
 struct SweepPlans {
     std::map<unsigned, SweepPlan> form;
-    std::map<unsigned, bool> possible;
+    std::map<unsigned, bool> possible, pays;
 };
 
 static SweepPlans &plans_of(const Matrix &A)
@@ -574,6 +578,76 @@ bool sweep_possible(const Matrix &A, int K, Prec p)
     return it != known.end() ? it->second : known.emplace(key, fits_lds(A, K, p)).first->second;
 }
 
+static int most_threads(Prec p) { return p == P64 ? sweep_threads<double>() : sweep_threads<float>(); }
+static int lanes_per_row(int K) { return K / (K == 8 ? kSweepR<8> : K == 4 ? kSweepR<4> : K == 2 ? kSweepR<2> : 1); }
+
+// The work of a half-sweep of `kind` in tiles: choose_tile's cost, on average
+// over the launches that a V-cycle makes on a level, or a sweep by itself.
+static double sweep_cost(const Matrix &A, int K, Prec p, int kind, bool cycle)
+{
+    auto cost = [&](bool forward, bool zero, bool skip_first, int tail) {
+        SweepArgs one{};
+        sweep_args(one, A.g, nullptr, 1, 1, forward, zero, skip_first, tail);
+        return (double)choose_tile(A.g, one, K, lanes_per_row(K), most_threads(p), vec_bytes(p)).cost;
+    };
+    if (kind == HPGMX_GS_SYMMETRIC) {
+        const double sweep = cost(true, false, false, 0) + cost(false, false, true, 0);
+        return cycle ? (cost(true, true, false, 0) + cost(false, false, true, 2) + sweep) / 4.0 : sweep / 2.0;
+    }
+    const bool forward = kind == HPGMX_GS_FORWARD;
+    const double sweep = cost(forward, false, false, 0);
+    return cycle ? (cost(forward, true, false, 1) + sweep) / 2.0 : sweep;
+}
+
+// Small levels gain the launches' latency in tiles; larger ones still gain,
+// because a tile's matrix entries are its values alone and its neighbours
+// come from LDS, until the halo rows cost more.  How many halo rows a tile
+// has depends on the x-lines: it keeps them whole, so long lines leave room
+// for few cells in y and z.  So the line is drawn by the work of the tiles
+// (sweep_cost) against what the colour launches cost, a part for the launches
+// and a part per row.  30-step solves with two levels, level 0 in tiles
+// against colour launches, with the cost in brackets (forward sweeps unless
+// named):
+//   FP32            256x128x120 -6 % (252)      360x100x100 +4 % (336)
+//                   440x96x96 +22 % (588)       440x40x40 backward -8 % (126)
+//                   440x64x64 +5 % (252)        400x100x104 +9 % (420)
+//   FP64            112^3 -5 % (180)            160x96x96 +1 % (222)
+//                   200x60x60 -9 % (156), symmetric +2 % (168)
+//                   220x80x88 +32 % (462)
+//   binary16        256x128x120 -7 % (252)      320x112x112 +2 % (336)
+//   bfloat16 hier.  512x100x80 -3 % (258)       640x80x80 +3 % (324)
+//                   600x60x60 -8 % (162)        900x16x16 +8 % (123)
+//   batches, FP32   4 x 100x64x64 -8 % (108), symmetric +6 % (117)
+//                   8 x 48^3 -11 % (90)         2 x 220x48x48 +13 % (150)
+//   batches, FP64   2 x 80^3 -8 % (132)         8 x 24x64x64 symmetric +1 % (117)
+// A sweep by itself has no restriction, and no SpMV after it that the colour
+// launches take a part of; but for FP64 and batches tiles pay further then:
+// FP32 440x96x96 -2 % (420), 420x140x70 -13 % (384); bfloat16 hierarchy
+// 640x80x80 -23 % (312), 900x16x16 +6 % (108); FP64 149x101x83 -15 % (192),
+// 200x88x88 +4 % (252); batches FP32 4 x 110x48x48 +9 % (120).
+// The most rows (times right-hand sides) come from cubes: FP32 160^3 19852 us
+// in colour launches and 18595 in tiles (4 levels); FP64 112^3 14003 and
+// 13589, but 128^3 17882 and 18273; batches FP32 2 x 96^3 8957 and 7434, but
+// 4 x 96^3 12312 and 14287; FP64 2 x 80^3 9388 and 8639, but 2 x 96^3 13636
+// and 13944.
+bool sweep_pays(const Matrix &A, int K, Prec p, int kind, bool cycle)
+{
+    const i64 rows = A.g.N * K, most = K == 1 ? (p == P64 ? 3 << 19 : 1 << 22) : (p == P64 ? 9 << 17 : 7 << 18);
+    if (rows > most || !sweep_possible(A, K, p)) return false;
+    auto &known = plans_of(A).pays;
+    const unsigned key = (unsigned)K << 6 | (unsigned)p << 3 | (unsigned)kind << 1 | (unsigned)cycle;
+    const auto it = known.find(key);
+    if (it != known.end()) return it->second;
+    // what eight colour launches cost: for the launches, and per 10^6 rows
+    double launches, per_row;
+    if (K > 1) launches = p == P64 ? 65.0 : 80.0, per_row = p == P64 ? 66.0 : 20.0;
+    else if (p == P64) launches = 122.0, per_row = 58.0;
+    else if (mg16(p)) launches = 75.0, per_row = cycle ? 54.0 : 60.0;
+    else launches = 120.0, per_row = cycle ? 53.0 : 75.0;
+    const bool pays = sweep_cost(A, K, p, kind, cycle) <= launches + per_row * 1e-6 * (double)rows;
+    return known.emplace(key, pays).first->second;
+}
+
 static SweepPlan make_plan(const Matrix &A, Prec p, int K, const Geom *gc, bool forward, bool zero, bool skip_first,
                            int tail)
 {
@@ -581,11 +655,11 @@ static SweepPlan make_plan(const Matrix &A, Prec p, int K, const Geom *gc, bool 
     SweepPlan o;
     SweepArgs one{};
     sweep_args(one, g, gc, 1, 1, forward, zero, skip_first, tail);
-    const int most = p == P64 ? sweep_threads<double>() : sweep_threads<float>();
-    const int L = K / (K == 8 ? kSweepR<8> : K == 4 ? kSweepR<4> : K == 2 ? kSweepR<2> : 1);
-    int n = 1, m = 1;
-    o.lds = choose_tile(g, one, K, L, most, vec_bytes(p), n, m);
-    if (o.lds == 0) throw std::runtime_error("launch_sweep: no tile fits the LDS");
+    const int most = most_threads(p), L = lanes_per_row(K);
+    const Tile t = choose_tile(g, one, K, L, most, vec_bytes(p));
+    if (t.lds == 0) throw std::runtime_error("launch_sweep: no tile fits the LDS");
+    const int n = t.n, m = t.m;
+    o.lds = t.lds;
     sweep_args(o.P, g, gc, n, m, forward, zero, skip_first, tail);
     o.P.remap = tile_remap(A);
     o.P.bytes = (unsigned)(ell_entries(g.N, A.clog2) * (i64)(p == P64 ? 8 : p == P32 ? 4 : 2));

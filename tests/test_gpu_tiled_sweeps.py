@@ -279,3 +279,37 @@ def test_colour_launches_every_tile_shape(hp, dims, levels, nrhs, dtype):
         finally:
             P.close()
             Q.close()
+
+
+@pytest.mark.parametrize("dims,dtype,nrhs,sweep,cycle,alone", [
+    ((160, 160, 160), 1, 1, "forward", True, True), ((256, 128, 120), 1, 1, "forward", True, True),
+    ((400, 100, 104), 1, 1, "forward", False, True), ((440, 96, 96), 1, 1, "symmetric", False, True),
+    ((440, 64, 64), 1, 1, "backward", False, True), ((112, 112, 112), 0, 1, "forward", True, True),
+    ((220, 80, 88), 0, 1, "forward", False, False), ((200, 60, 60), 0, 1, "backward", False, True),
+    ((160, 160, 160), 4, 1, "forward", True, True), ((640, 80, 80), 5, 1, "forward", False, True),
+    ((900, 16, 16), 5, 1, "symmetric", False, False), ((256, 128, 120), 2, 1, "forward", True, True),
+    ((400, 100, 104), 2, 1, "backward", False, True), ((96, 96, 96), 1, 2, "symmetric", True, True),
+    ((220, 48, 48), 1, 2, "forward", False, False), ((110, 48, 48), 1, 4, "symmetric", False, False),
+    ((48, 64, 64), 1, 8, "backward", False, True), ((80, 80, 80), 0, 2, "forward", True, True)])
+def test_long_lines_keep_the_colour_launches(hp, dims, dtype, nrhs, sweep, cycle, alone):
+    """Levels where half-sweeps in tiles were measured slower, because a tile of whole x-lines leaves room for few
+    cells in y and z, take a launch per colour: in a V-cycle (`cycle`: level 0 runs in tiles), or for a sweep by
+    itself from given values (`alone`), where tiles pay further."""
+    import torch
+    P = hp.Problem(dims, levels=2, sweep=sweep, stream=torch.cuda.Stream())
+    code = {"forward": hp.GS_FORWARD, "backward": hp.GS_BACKWARD, "symmetric": hp.GS_SYMMETRIC}[sweep]
+    half = 2 if sweep == "symmetric" else 1
+    try:
+        r = torch.zeros((nrhs, P.N), device="cuda", dtype=getattr(torch, VEC.get(dtype, "float32")))
+        z = torch.zeros_like(r)
+        if nrhs == 1:
+            n = [launches(hp, P, f) for f in (lambda: hp.smooth(P.h, 0, dtype, code, r[0], z[0]),
+                                              lambda: hp.vcycle(P.h, dtype, r[0], z[0]))]
+        else:
+            n = [launches(hp, P, f) for f in (lambda: hp.smooth_batched(P.h, 0, dtype, code, r, z),
+                                              lambda: hp.vcycle_batched(P.h, dtype, r, z))]
+        assert n[0] - 3 == (half if alone else 8 * half - half // 2)  # beside two permutations in and one out
+        # beside a permutation each way, level 0 in tiles takes a launch per half-sweep (level 1 up to eight)
+        assert (n[1] - 2 <= 2 * half + 8 * half) == cycle, n[1]
+    finally:
+        P.close()
