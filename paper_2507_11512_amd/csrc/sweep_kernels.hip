@@ -525,8 +525,10 @@ template <typename V, typename S, int K, bool SPLIT>
 void sweep_launch(const V *v, const V *d, const SweepArgs &P, int tiles, int threads, size_t lds, const void *r,
                   const void *zin, const void *zc, void *zout, void *rc, hipStream_t s)
 {
+    // the most any launch takes, not this one's: the setting is the kernel's,
+    // shared by every handle and thread of the process
     if (lds > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sweep<V, S, K, kSweepR<K>, SPLIT>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSweepLds) != hipSuccess)
         throw std::runtime_error("launch_sweep: the device refuses the workgroup's LDS");
     hipLaunchKernelGGL((k_sweep<V, S, K, kSweepR<K>, SPLIT>), dim3(tiles), dim3(threads), lds, s, P, v, d, (const S *)r, (const S *)zin,
                        (const S *)zc, (S *)zout, (S *)rc);

@@ -313,3 +313,38 @@ def test_long_lines_keep_the_colour_launches(hp, dims, dtype, nrhs, sweep, cycle
         assert (n[1] - 2 <= 2 * half + 8 * half) == cycle, n[1]
     finally:
         P.close()
+
+
+def test_handles_on_two_threads(hp):
+    """Two threads with a handle each, whose tiles take different amounts of LDS in the same kernel: the limit that a
+    launch asks for is the kernel's, so each must leave it high enough for the other."""
+    import threading
+
+    import torch
+    shapes = [(320, 64, 48), (200, 152, 104)]
+    Ps = [hp.Problem(d, levels=2, stream=torch.cuda.Stream()) for d in shapes]
+    rs = [vec(d, 95, 1) for d in shapes]
+    refs = [torch.empty_like(r) for r in rs]
+    for P, r, z in zip(Ps, rs, refs):
+        hp.vcycle(P.h, 1, r, z)
+    torch.cuda.synchronize()
+    bad = []
+
+    def work(P, r, ref):
+        try:
+            z = torch.empty_like(r)
+            for _ in range(200):
+                hp.vcycle(P.h, 1, r, z)
+            P.stream.synchronize()
+            if not torch.equal(z, ref):
+                bad.append("result")
+        except Exception as e:
+            bad.append(e)
+    threads = [threading.Thread(target=work, args=a) for a in zip(Ps, rs, refs)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for P in Ps:
+        P.close()
+    assert not bad, bad
