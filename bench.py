@@ -95,18 +95,51 @@ def parse(argv=None):
     return ap.parse_args(argv)
 
 
-def vcycle_bytes(cfg, B, hp, pm, colour, restrict_after, restrict_full, prolong):
+def tiled_levels(hp, handle, cfg, cycles):
+    """Levels whose half sweeps ran as one launch each in the profiled solve:
+    one launch from zero per V-cycle there, at least four in colour launches.
+    (A profiled solve whose level 0 takes colour launches takes them on every
+    level; others run the coarser levels in one launch per half sweep.)"""
+    vcycles = sum(cycles) + len(cycles)
+    return {l for l in range(cfg.levels) if hp.profile_get(handle, hp.K_GS_ZERO, l)[1] == vcycles}
+
+
+def tiled_level_bytes(cfg, B, hp, pm, l, cr, rc, half):
+    """The level's part of vcycle_bytes() where it runs in tiles (half: as
+    pm.tiled_half_bytes without its dtype)."""
+    fwd, sym = cfg.sweep != 1, cfg.sweep == 2
+    coarsest = l == cfg.levels - 1
+    active = sum(pm.zero_guess_active_slots(c, fwd) for c in range(8))
+
+    def slots(i):      # colours relaxed; the backward half of a symmetric sweep skips its first one
+        return cr * pm.SLOTS * (7 if sym and i % 2 else 8)
+    n = (cfg.coarsest if coarsest else cfg.pre) * (2 if sym else 1)
+    for i in range(n):
+        down = i == n - 1 and not coarsest
+        late = ((8 if fwd else 18) if n == 1 else pm.SLOTS) if down else 0   # slots of the restriction
+        B[(hp.K_GS if i else hp.K_GS_ZERO, l)] += half(8 * cr, (slots(i) if i else cr * active) + rc * late,
+                                                       start=i > 0, coarse=rc if down else 0)
+    if not coarsest:
+        for i in range(cfg.post * (2 if sym else 1)):
+            B[(hp.K_GS, l)] += half(8 * cr, slots(i), start=True, coarse=0 if i else rc)
+
+
+def vcycle_bytes(cfg, B, hp, pm, colour, restrict_after, restrict_full, prolong, tiled=(), half=None):
     """Adds the algorithmic bytes of one V-cycle to B[(kernel id, level)].
     colour(rows, slots): one colour launch over `rows` rows reading `slots`
     off-diagonal slots; restrict_after(rc, slots): the restriction after a
     single sweep from zero; restrict_full(rc), prolong(rc): the general
-    restriction and the prolongation onto rc coarse rows."""
+    restriction and the prolongation onto rc coarse rows; tiled: the levels
+    whose half sweeps are one launch each, with half as tiled_level_bytes()."""
     L = pm.level_dims(cfg.dims, cfg.levels)
     fwd, sym = cfg.sweep != 1, cfg.sweep == 2
     per_sweep = 15 if sym else 8   # the backward half of a symmetric sweep skips its first colour
     for l, d in enumerate(L):
         cr = pm.nrows(d) // 8      # even dims on every level but possibly the coarsest
         coarsest = l == cfg.levels - 1
+        if l in tiled:
+            tiled_level_bytes(cfg, B, hp, pm, l, cr, 0 if coarsest else pm.nrows(L[l + 1]), half)
+            continue
         nsw = cfg.coarsest if coarsest else cfg.pre
         if nsw > 0:                # the first sweep starts from zero
             for c in range(8):
@@ -123,14 +156,15 @@ def vcycle_bytes(cfg, B, hp, pm, colour, restrict_after, restrict_full, prolong)
             B[(hp.K_PROLONG, l)] += prolong(rc)
 
 
-def kernel_bytes_table(cfg, cycles, dtype, hp, pm, idx=4, spmv_in_sweep=2):
+def kernel_bytes_table(cfg, cycles, dtype, hp, pm, idx=4, spmv_in_sweep=2, tiled=()):
     """Algorithmic bytes per (kernel id, level) over one solve with the given
     cycles (idx: bytes of a stored column index).  spmv_in_sweep as the
     library's layout setting: with 1 the last colour launch of each inner
     V-cycle also writes its colour's rows of w = A z and the SpMV covers the
     other 7/8 of the rows; with 2 (the default) the launches at sweep
     positions 2-6 also write partial sums of their rows, and the SpMV reads
-    only the remaining slots of those rows."""
+    only the remaining slots of those rows.  tiled: the levels in tiles; with
+    level 0 among them the SpMV covers all rows."""
     from collections import defaultdict
     B = defaultdict(float)
 
@@ -139,11 +173,12 @@ def kernel_bytes_table(cfg, cycles, dtype, hp, pm, idx=4, spmv_in_sweep=2):
                      lambda rows, slots: pm.gs_colour_bytes(rows, slots, dtype, idx),
                      lambda rc, slots: pm.restrict_after_sweep_bytes(rc, dtype, slots, idx=idx),
                      lambda rc: pm.restrict_bytes(rc, dtype, idx),
-                     lambda rc: pm.prolong_bytes(rc, dtype))
+                     lambda rc: pm.prolong_bytes(rc, dtype), tiled,
+                     lambda *a, **k: pm.tiled_half_bytes(dtype, *a, **k))
 
     N = pm.nrows(cfg.dims)
     w = pm.wb(dtype)
-    fused = spmv_in_sweep in (1, 2) and cfg.levels > 1 and cfg.post >= 1
+    fused = spmv_in_sweep in (1, 2) and cfg.levels > 1 and cfg.post >= 1 and 0 not in tiled
     split = fused and spmv_in_sweep == 2
     last = N // 8 if fused else 0   # rows of the last colour (even grids)
     fwd = cfg.sweep == 0
@@ -175,7 +210,7 @@ def kernel_bytes_table(cfg, cycles, dtype, hp, pm, idx=4, spmv_in_sweep=2):
     return B
 
 
-def kernel_bytes_table_batched(cfg, cycles, dtype, K, hp, pm, spmv_in_sweep=2):
+def kernel_bytes_table_batched(cfg, cycles, dtype, K, hp, pm, spmv_in_sweep=2, tiled=()):
     """As kernel_bytes_table for K right-hand sides in lockstep (the partial
     SpMV sums of spmv_in_sweep = 2 for FP32 and FP64 batches)."""
     from collections import defaultdict
@@ -186,11 +221,12 @@ def kernel_bytes_table_batched(cfg, cycles, dtype, K, hp, pm, spmv_in_sweep=2):
                      lambda rows, slots: pm.bgs_colour_bytes(rows, slots, dtype, K),
                      lambda rc, slots: pm.restrict_after_sweep_bytes(rc, dtype, slots, K),
                      lambda rc: pm.brestrict_bytes(rc, dtype, K),
-                     lambda rc: pm.bprolong_bytes(rc, dtype, K))
+                     lambda rc: pm.bprolong_bytes(rc, dtype, K), tiled,
+                     lambda *a, **k: pm.tiled_half_bytes(dtype, *a, K=K, **k))
 
     N = pm.nrows(cfg.dims)
     w = pm.wb(dtype)
-    split = spmv_in_sweep in (2,) and dtype in (0, 1) and cfg.levels > 1 and cfg.post >= 1
+    split = spmv_in_sweep in (2,) and dtype in (0, 1) and cfg.levels > 1 and cfg.post >= 1 and 0 not in tiled
     last = N // 8 if split else 0
     fwd = cfg.sweep == 0
     late = [26 - pm.zero_guess_active_slots(c if fwd else 7 - c, fwd) for c in range(2, 7)] if split else []
@@ -218,7 +254,7 @@ def kernel_bytes_table_batched(cfg, cycles, dtype, K, hp, pm, spmv_in_sweep=2):
 def source_sha():
     h = hashlib.sha256()
     for f in ("stencil_kernels.hip", "krylov_kernels.hip", "krylov_batch.hip", "batch_kernels.hip",
-              "hpgmx_internal.hpp", "ell_device.hpp", "krylov_device.hpp"):
+              "sweep_kernels.hip", "hpgmx_internal.hpp", "ell_device.hpp", "krylov_device.hpp"):
         with open(os.path.join(ROOT, "paper_2507_11512_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -328,8 +364,11 @@ def main():
     prof_precs = () if args.no_profile else (("mxp", inner_code),) if args.no_fp64 else (("mxp", inner_code), ("fp64", hp.F64))
     for prec, dt_code in prof_precs:
         _, st = P.solve(b, tol=0.0, restart=m, max_iters=args.iters, precision=PREC[prec], profile=True)
-        profile_kernels(hp, P.h, kernel_bytes_table(cfg, cycles, dt_code, hp, pm, idx), prec, kernels)
-        log(f"profiled {prec} solve: {st.solve_ms:.1f} ms with events")
+        tiles = tiled_levels(hp, P.h, cfg, cycles)
+        profile_kernels(hp, P.h, kernel_bytes_table(cfg, cycles, dt_code, hp, pm, idx, tiled=tiles), prec, kernels)
+        log(f"profiled {prec} solve: {st.solve_ms:.1f} ms with events, " +
+            (f"half sweeps in one launch on levels {sorted(tiles)}" if tiles else
+             "a launch per colour on every level (timed solves: half sweeps in one launch on small coarser levels)"))
     mxp_k = {k: v for k, v in kernels.items() if k.endswith("_mxp")}
     dom_name = max(mxp_k, key=lambda k: mxp_k[k]["total_ms"]) if mxp_k else None
     dominant = mxp_k[dom_name] if mxp_k else None
@@ -600,7 +639,8 @@ def run_batched(args, hp, pm, torch, np):
             _, sts = P.solve_batched(B, tol=0.0, restart=m, max_iters=args.iters, precision=PREC[prec],
                                      profile=True)
             profile_kernels(hp, P.h, kernel_bytes_table_batched(cfg, cycles, code, 8 if k > 4 else (4 if k > 2 else 2),
-                                                                hp, pm), prec, kernels)
+                                                                hp, pm, tiled=tiled_levels(hp, P.h, cfg, cycles)),
+                            prec, kernels)
             log(f"profiled batched {prec} solve: {sts[0].solve_ms:.1f} ms with events")
     mxp_k = {kk_: v for kk_, v in kernels.items() if kk_.endswith("_mxp")}
     dom_name = max(mxp_k, key=lambda q: mxp_k[q]["total_ms"]) if mxp_k else None

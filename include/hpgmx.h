@@ -198,11 +198,11 @@ hpgmx_status hpgmx_set_column_format(hpgmx_handle h, int format);
  *                  extent: the first two pairs of the sweep on levels with
  *                  at most pair_rows rows per colour, the last two on
  *                  levels with at most pair_rows / 64; 0 = never (default
- *                  2^17).  With the default, and without profiling, levels
- *                  of up to 2^22 rows (3 * 2^19 in FP64; batches 7 * 2^18
- *                  rows times right-hand sides, 9 * 2^17 in FP64) run each
- *                  half sweep as one launch instead, unless their x-lines
- *                  are so long that this is slower.
+ *                  2^17).  With the default, levels of up to 2^22 rows
+ *                  (3 * 2^19 in FP64; batches 7 * 2^18 rows times
+ *                  right-hand sides, 9 * 2^17 in FP64) run each half sweep
+ *                  as one launch instead, unless their x-lines are so long
+ *                  that this is slower.
  *   spmv_in_sweep  how the solver's SpMV w = A z after each V-cycle shares
  *                  work with the V-cycle's last level-0 sweep.  0: one SpMV
  *                  over all rows.  1: the sweep's last colour launch (whose
@@ -321,12 +321,18 @@ hpgmx_status hpgmx_stencil_grad(hpgmx_handle h, const double *lam, const double 
  * before any solve has run.  Stream-ordered. */
 hpgmx_status hpgmx_stencil_grad_noalloc(hpgmx_handle h, const double *lam, const double *x, double *out27);
 
-/* Per-kernel timing of the last solve run with HPGMX_SOLVE_PROFILE.
+/* Per-kernel timing of the last solve run with HPGMX_SOLVE_PROFILE.  It makes
+ * the launches that a solve without it makes (from the host, not replayed),
+ * except that a solve whose level 0 takes a launch per colour takes them on
+ * the coarser levels too, where other solves may run each half sweep as one
+ * launch (see pair_rows).
  * Kernel ids are HPGMX_K_*; `level` selects the grid for the per-level
  * kernels (ignored otherwise).  Returns the summed device time in ms and the
  * number of launches. */
-#define HPGMX_K_GS 0           /* one colour of a Gauss-Seidel sweep          */
-#define HPGMX_K_GS_ZERO 1      /* one colour of a sweep from a zero guess     */
+#define HPGMX_K_GS 0           /* one colour of a Gauss-Seidel sweep, or a half sweep
+                                  in one launch (see pair_rows; the restriction or the
+                                  prolongation that goes with it included)    */
+#define HPGMX_K_GS_ZERO 1      /* the same from a zero guess                  */
 #define HPGMX_K_RESTRICT 2     /* fused residual-restriction                  */
 #define HPGMX_K_PROLONG 3      /* prolongation-correction                    */
 #define HPGMX_K_SPMV_DOT 4     /* reserved (a fused SpMV + GEMVT; not launched) */

@@ -308,12 +308,18 @@ void *gathered_vector(hpgmx_ctx *c, i64 N, Prec p)
 void *entry(void *v, i64 N, Prec p) { return (char *)v + (size_t)N * vec_bytes(p); }
 
 // Whether the half-sweeps of sweeps of `kind` on level l, in a V-cycle or by
-// themselves, run as one launch each, where that is the faster way (sweep_pays).  A handle with a pair_rows
-// of its own gets the launches it asks for, and a profiled solve the launches
-// that are timed one by one.
+// themselves, run as one launch each, where that is the faster way
+// (sweep_pays).  A handle with a pair_rows of its own gets the launches it
+// asks for.  A profiled solve whose level 0 takes colour launches takes them
+// on every level: the values that a tiled level 1 loads stay in the caches,
+// which the level-0 rates would show (the post-sweep of 320^3 0.717 of the
+// peak, 0.709 with them; keeping them out by nontemporal loads costs the tiles
+// more, a 200x152x104 V-cycle 439 -> 523 us).
 bool tiled(const hpgmx_ctx *c, int l, Prec p, int K, int kind, bool cycle)
 {
-    return !c->prof && c->layout.pair_rows == kDefaultPairRows && sweep_pays(c->lv[l].A, K, p, kind, cycle);
+    if (c->layout.pair_rows != kDefaultPairRows) return false;
+    if (c->prof && l > 0 && !sweep_pays(c->lv[0].A, K, p, kind, cycle)) return false;
+    return sweep_pays(c->lv[l].A, K, p, kind, cycle);
 }
 
 void ensure_level_vectors(hpgmx_ctx *c, Prec p)
@@ -483,6 +489,7 @@ void tiled_sweeps(hpgmx_ctx *c, int l, Prec p, int K, int kind, int nsweeps, con
         const bool symm = kind == HPGMX_GS_SYMMETRIC, back = symm ? (h & 1) : kind == HPGMX_GS_BACKWARD;
         void *dst = (half - h) & 1 ? z : other;
         const bool last = h == half - 1;
+        ProfScope ps(c, src ? HPGMX_K_GS : HPGMX_K_GS_ZERO, l);
         // the backward half of a symmetric sweep leaves colour 7 as it is: its neighbours are unchanged
         launch_sweep(c->lv[l].A, p, K, !back, symm && back, r, src,
                      l + 1 < (int)c->lv.size() ? &c->lv[l + 1].A.g : nullptr, h == 0 ? zc : nullptr, dst,

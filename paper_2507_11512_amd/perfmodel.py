@@ -148,6 +148,15 @@ def gs_colour_bytes(rows, active_slots, dtype, idx=IDX):
     return rows * (active_slots * (v + idx) + v + (3 if active_slots else 2) * w)
 
 
+def tiled_half_bytes(dtype, rows, slots, start=False, coarse=0, K=1):
+    """A half sweep in one launch: `slots` matrix values (no columns), the
+    diagonal, r read, z written, the old z read unless it starts from zero,
+    and `coarse` rows of the coarser level read (prolongation) or written
+    (restriction, its slots among `slots`); K vectors."""
+    v, w = vb(dtype), mgb(dtype)
+    return slots * v + rows * (v + (3 if start else 2) * K * w) + coarse * K * w
+
+
 def spmv_bytes(rows, dtype, idx=IDX):
     """The SpMV of an inner step: x is the V-cycle's output (a multigrid
     vector), y a Krylov vector."""

@@ -348,3 +348,37 @@ def test_handles_on_two_threads(hp):
     for P in Ps:
         P.close()
     assert not bad, bad
+
+
+@pytest.mark.parametrize("sweep", ["forward", "backward", "symmetric"])
+@pytest.mark.parametrize("nrhs", [1, 3])
+def test_profile_times_the_launches_of_the_solve(hp, sweep, nrhs):
+    """A profiled solve makes the launches of any other where level 0 runs in tiles: every level counts one per
+    half-sweep, with the restriction and the prolongation in it, and the byte model prices them as such."""
+    import torch
+
+    import bench
+    from paper_2507_11512_amd import perfmodel as pm
+    dims, V, half = (32, 48, 40), 31, 2 if sweep == "symmetric" else 1
+    cfg = pm.Config(dims=dims, levels=3, sweep=bench.SWEEP_CODE[sweep])
+    for lay, tiles in ((None, True), ({"pair_rows": 0}, False)):
+        P = hp.Problem(dims, levels=3, sweep=sweep, layout=lay)
+        try:
+            b = P.rhs_from_x(vec(dims, 96, 0))
+            B = torch.stack([b, 2 * b, b.flip(0)])
+            kw = dict(tol=0.0, restart=30, max_iters=30)
+            x = [P.solve(b, profile=p, **kw)[0] if nrhs == 1 else P.solve_batched(B, profile=p, **kw)[0]
+                 for p in (False, True)]
+            assert torch.equal(x[0], x[1])
+            n = {(k, l): hp.profile_get(P.h, k, l)[1] for l in range(3)
+                 for k in (hp.K_GS, hp.K_GS_ZERO, hp.K_RESTRICT, hp.K_PROLONG)}
+            assert bench.tiled_levels(hp, P.h, cfg, [30]) == ({0, 1, 2} if tiles else set())
+            T = bench.kernel_bytes_table(cfg, [30], 1, hp, pm, tiled={0, 1, 2} if tiles else ())
+            for l in range(3):
+                if tiles:
+                    assert n[hp.K_GS_ZERO, l] == V and n[hp.K_GS, l] == V * (2 * half - 1 if l < 2 else half - 1)
+                    assert n[hp.K_RESTRICT, l] == n[hp.K_PROLONG, l] == 0
+                for k in (hp.K_GS, hp.K_GS_ZERO, hp.K_RESTRICT, hp.K_PROLONG):
+                    assert (T.get((k, l), 0) > 0) == (n[k, l] > 0)
+        finally:
+            P.close()

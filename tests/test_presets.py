@@ -114,3 +114,26 @@ def test_fused_spmv_rows_in_the_tables():
     one = pm.Config(dims=(64, 64, 64), levels=1, sweep=0)   # no post-sweep on level 0: nothing fused
     assert bench.kernel_bytes_table(one, [5], 1, H, pm) == bench.kernel_bytes_table(one, [5], 1, H, pm,
                                                                                   spmv_in_sweep=0)
+
+
+def test_levels_in_tiles_in_the_tables():
+    """A level whose half-sweeps are one launch each reads its matrix values once per half-sweep and no columns, and
+    moves the coarse vectors of the restriction and the prolongation with them; the SpMV is whole."""
+    class H:
+        K_GS, K_GS_ZERO, K_RESTRICT, K_PROLONG = 0, 1, 2, 3
+        K_SPMV, K_DOT, K_CGS_DOT, K_CGS_NORM, K_RESID64, K_CAST = 4, 5, 6, 7, 8, 9
+        K_FINISH, K_GEMV, K_UPDATE, K_PERMUTE = 10, 11, 12, 13
+        F16_MG, BF16_MG = 4, 5
+    N = [64 ** 3, 32 ** 3]
+    for sweep in (0, 1):
+        cfg = pm.Config(dims=(64, 64, 64), levels=2, sweep=sweep)
+        T = bench.kernel_bytes_table(cfg, [5], 1, H, pm, tiled={0, 1})
+        # from zero: half of the 26 slots, the diagonal, r, z; with the restriction its 8 (18) slots and r_c
+        assert T[(H.K_GS_ZERO, 0)] == 6 * (N[0] * (13 * 4 + 4 + 8) + N[1] * ((8 if sweep == 0 else 18) * 4 + 4))
+        assert T[(H.K_GS_ZERO, 1)] == 6 * N[1] * (13 * 4 + 4 + 8)
+        assert T[(H.K_GS, 0)] == 6 * (N[0] * (26 * 4 + 4 + 12) + N[1] * 4)   # old z, and z_c of the prolongation
+        assert T.get((H.K_RESTRICT, 0), 0) == T.get((H.K_PROLONG, 0), 0) == T.get((H.K_GS, 1), 0) == 0
+        assert T[(H.K_SPMV, 0)] == 5 * pm.spmv_bytes(N[0], 1)
+    cfg = pm.Config(dims=(64, 64, 64), levels=2, sweep=2)
+    T = bench.kernel_bytes_table_batched(cfg, [5], 1, 8, H, pm, tiled={1})
+    assert T[(H.K_GS, 1)] == 6 * N[1] * (26 * 4 * 7 / 8 + 4 + 8 * 12)        # the backward half
