@@ -382,3 +382,42 @@ def test_profile_times_the_launches_of_the_solve(hp, sweep, nrhs):
                     assert (T.get((k, l), 0) > 0) == (n[k, l] > 0)
         finally:
             P.close()
+
+
+@pytest.mark.parametrize("dims,dtype,nrhs", [((64, 64, 64), 1, 1), ((320, 64, 48), 1, 1), ((96, 80, 64), 0, 1),
+                                             ((40, 48, 56), 1, 3)])
+def test_captured_cycle(hp, dims, dtype, nrhs):
+    """A program that captures a V-cycle: replays on new inputs, with the program's own work between them."""
+    import torch
+    P = hp.Problem(dims, levels=3, stream=torch.cuda.Stream())
+    try:
+        rs = [torch.stack([vec(dims, 97 + 5 * i + j, dtype) for j in range(nrhs)]) for i in range(3)]
+        r, z = rs[0].clone(), torch.zeros_like(rs[0])
+
+        def cycle():
+            if nrhs == 1:
+                hp.vcycle(P.h, dtype, r[0], z[0])
+            else:
+                hp.vcycle_batched(P.h, dtype, r, z)
+        torch.cuda.synchronize()
+        refs = []
+        for x in rs:
+            r.copy_(x)
+            torch.cuda.synchronize()
+            cycle()
+            torch.cuda.synchronize()
+            refs.append(z.clone())
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=P.stream):
+            cycle()
+        for _ in range(2):
+            for x, ref in zip(rs, refs):
+                r.copy_(x)
+                z.zero_()
+                torch.cuda.synchronize()
+                g.replay()
+                torch.cuda.synchronize()
+                assert torch.equal(z, ref)
+                assert torch.equal((2 * x).sum(), (x + x).sum())  # other work between the replays
+    finally:
+        P.close()
