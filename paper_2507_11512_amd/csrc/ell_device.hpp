@@ -150,7 +150,6 @@ __device__ __forceinline__ T ell_row_dot(const V *__restrict__ offv, const void 
     return acc;
 }
 
-
 // One SpMV row from its parts: (a_pp x_p + acc) * scale, acc the slot sum of
 // ell_row_dot.  Contraction is off so that the SpMV kernel and the last
 // Gauss-Seidel colour launch, which computes the rows of its colour (see
@@ -221,9 +220,13 @@ __device__ __forceinline__ T ell_row_dot2(const V *__restrict__ offv, const void
 
 // Largest level (rows times right-hand sides) whose split sums, where the
 // sweep left none, are formed in one launch rather than in one per colour.  It
-// reads what those read; a 30-step cycle takes 3204 instead of 3843 us at
-// 24^3, 6613 instead of 7014 at 96^3 and 8351 instead of 8672 at 112^3 in
-// FP32; from 128^3 on the two are within 0.5 % (144^3: 14566 and 14544).
+// reads what those read; a 30-step cycle with level 0 in tiles (us, a launch
+// per colour and one): FP32 48^3 2857 and 2229, 96^3 5120 and 4670, 128^3 8616
+// and 8434; FP64 96^3 7696 and 7168, 112^3 11817 and 11486; binary16 128^3
+// 7716 and 7447, bfloat16 hierarchy 8033 and 7643; 16-bit offsets, FP32 128^3
+// 8188 and 7779; batches FP32 2 x 96^3 6569 and 6066, 8 x 48^3 5506 and 4915,
+// FP64 4 x 48^3 5319 and 4727.  On larger grids the two are within 0.5 %
+// (FP32 144^3, four levels: 14566 and 14544).
 constexpr i64 kSpmvOneLaunch = 1 << 21;
 
 // The slots E of launch_spmv_split per colour (none for the whole rows).

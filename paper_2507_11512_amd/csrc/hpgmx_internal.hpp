@@ -324,12 +324,11 @@ bool gs_pair_possible(const Matrix &A);
 // launch also restricts the residual of zout, as launch_restrict_after_sweep
 // for a sweep from zero and as launch_restrict otherwise.  skip_first: the
 // first colour is left as it is in zin.  K interleaved right-hand sides.
-bool sweep_possible(const Matrix &A, int K, Prec p);
-// Whether such launches are the faster way for sweeps of `kind` (hpgmx_sweep),
-// in a V-cycle or by themselves.
-bool sweep_pays(const Matrix &A, int K, Prec p, int kind, bool cycle);
 void launch_sweep(const Matrix &A, Prec p, int K, bool forward, bool skip_first, const void *r, const void *zin,
                   const Geom *gc, const void *zc, void *zout, void *rc, hipStream_t s);
+// Whether such launches are possible and the faster way for sweeps of `kind`
+// (hpgmx_sweep), in a V-cycle or by themselves.
+bool sweep_pays(const Matrix &A, int K, Prec p, int kind, bool cycle);
 void launch_restrict(const Matrix &Af, const Geom &gc, Prec p, const void *r, const void *z,
                      void *rc, hipStream_t s);
 // The same result when z is the outcome of a single Gauss-Seidel sweep from

@@ -574,7 +574,7 @@ static bool fits_lds(const Matrix &A, int K, Prec p)
     return true;
 }
 
-bool sweep_possible(const Matrix &A, int K, Prec p)
+static bool sweep_possible(const Matrix &A, int K, Prec p)
 {
     if (A.clog2 != kDefaultEllChunkLog2 || A.g.N * K > (1 << 22)) return false;
     auto &known = plans_of(A).possible;
