@@ -621,7 +621,7 @@ static double sweep_cost(const Matrix &A, int K, Prec p, int kind, bool cycle)
 //                   220x80x88 +32 % (462)
 //   binary16        256x128x120 -7 % (252)      320x112x112 +2 % (336)
 //   bfloat16 hier.  512x100x80 -3 % (258)       640x80x80 +3 % (324)
-//                   600x60x60 -8 % (162)        900x16x16 +8 % (123)
+//                   600x60x60 -8 % (162)        900x16x16 +8 % (126)
 //   batches, FP32   4 x 100x64x64 -8 % (108), symmetric +6 % (117)
 //                   8 x 48^3 -11 % (90)         2 x 220x48x48 +13 % (150)
 //   batches, FP64   2 x 80^3 -8 % (132)         8 x 24x64x64 symmetric +1 % (117)
